@@ -80,7 +80,8 @@ Layout layout_for(int op, int dtype, int d, const Batch& bt, const int64_t* cu =
     L.rcol = off;
     off = align_up(off + 4 * np);
     L.prank = off;
-    off = align_up(off + 4 * np);
+    L.best = off + candidates_offset(np);
+    off = align_up(L.best + 16 * np);
     L.pmeta = off;
     off = align_up(off + sizeof(ProblemMeta) * (size_t)bt.n_heads * bt.n_seqs);
     const size_t dcol = dtype == TWINKV_F32 ? (size_t)(2 * d) : (size_t)d;
@@ -117,9 +118,11 @@ int check_keys(const void* keys, int dtype, int d, int64_t head_stride, int64_t 
   return TWINKV_OK;
 }
 
-// Builds the per-sequence table (schedule of similarity row blocks, longest first).
+// Builds the per-sequence table (schedule of similarity row blocks, longest first; row_pad rows more
+// per sequence than it has tokens).
 std::vector<SeqInfo> seq_table(const int64_t* cu, int n_seqs, const int64_t* budget, int rows_per_block,
-                               int& total_tiles, int prep_tokens = 0, int64_t* prep_blocks = nullptr) {
+                               int& total_tiles, int prep_tokens = 0, int64_t* prep_blocks = nullptr,
+                               int row_pad = 0) {
   std::vector<SeqInfo> tab(n_seqs);
   int64_t pb = 0;
   for (int s = 0; s < n_seqs; ++s) {
@@ -138,7 +141,9 @@ std::vector<SeqInfo> seq_table(const int64_t* cu, int n_seqs, const int64_t* bud
   int cum = 0;
   for (int r = 0; r < n_seqs; ++r) {
     const int s = order[r];
-    const int nb = rows_per_block > 0 ? (tab[s].len + rows_per_block - 1) / rows_per_block : 0;
+    const int nb = rows_per_block > 0 && tab[s].len > 0
+                       ? (int)(((int64_t)tab[s].len + row_pad + rows_per_block - 1) / rows_per_block)
+                       : 0;
     tab[r].sorted_seq = s;
     tab[r].tile_cum = cum;
     tab[r].nb = nb;
@@ -188,10 +193,13 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
                    const uint8_t* retained, int32_t* status, char* ws, const Layout& L,
                    bool copy_evicted, void* stream, Prepared& P, bool key_prep = true) {
   int total_tiles = 0;
-  const int rpb = sim_rows_per_block(dtype, d);
+  // the rows of the all-pairs sweep are slots of the column list, counted at its largest padding
+  // (both groups end with a partly filled unit); those of the S0 sweep are tokens
+  const int rpb = copy_evicted ? sim_rows_per_block(dtype, d) : sim_retained_rows_per_block(dtype, d);
+  const int row_pad = copy_evicted ? kPermPad - 2 : 0;
   int64_t prep_blocks = 0;
   std::vector<SeqInfo> tab = seq_table(cu, bt.n_seqs, budget, rpb, total_tiles,
-                                       prepare_tokens_per_block(dtype, d), &prep_blocks);
+                                       prepare_tokens_per_block(dtype, d), &prep_blocks, row_pad);
   if (prep_blocks > (int64_t)INT32_MAX) return TWINKV_E_ARG;
   P.prep_blocks = (int)prep_blocks;
   const int64_t groups = bt.n_heads >= 8 ? 8LL * ((bt.n_heads + 7) / 8) : bt.n_heads;
@@ -250,6 +258,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   a.arg_all = nullptr;
   a.best_ret = nullptr;
   a.arg_ret = nullptr;
+  a.best = reinterpret_cast<unsigned long long*>(ws + L.best);
   return TWINKV_OK;
 }
 

@@ -4,650 +4,729 @@
 // N x N matrix (Sec. 3.2 Eq. 1 and the twin window; Sec. 3.4 Eq. 4):
 //   best over all j with |i-j| > w of sim(i, j)        -> best_all / arg_all
 //   best over j in S0 with |i-j| > w of sim(i, j)      -> best_ret / arg_ret  (= b_i(S0))
-// with sim(i, j) = (k_i . k_j) * r_i * r_j, r = 1 / ||k||.  In count mode (Sec. 3.2 Eq. 2)
-// the same sweep instead counts, per token, the j with |i-j| > w and sim(i, j) > tau.
+// In count mode (Sec. 3.2 Eq. 2) the same sweep counts, per token, the j with |i-j| > w and
+// sim(i, j) > tau.
+//
+// sim(i, j) = sim(j, i), so every unordered pair is computed once and reduced into both of its
+// tokens.  Tokens are addressed by their slot in the partitioned order [S0 | evicted] of the
+// column copy; keys there are scaled by an exact power of two to a norm in (0.5, 1], and
+// r' = 1 / ||scaled key|| lies in [1, 2).
 //
 // Mapping onto gfx950:
-//  * One workgroup owns RB = NWAVES * NSUB * 32 consecutive rows of one problem; each wave
-//    holds NSUB 32-row blocks of its row keys as MFMA B operands in registers for the whole
-//    sweep (d <= 128 makes this a short-K contraction).
-//  * Column keys stream through LDS in tiles of TN = 32 * CPT columns, double buffered, from
-//    the contiguous copy in partitioned order [S0 | evicted] written by the key preparation,
-//    so every 32-column chunk belongs to exactly one of the two reductions and tile loads
-//    are plain streams.
-//  * v_mfma_f32_32x32x16_bf16 with A = 32 column keys, B = 32 row keys gives each lane one
-//    row i (lane % 32) and 16 columns: register v holds column 8*(v/4) + 4*(lane/32) + v%4.
-//  * Row keys are pre-scaled by an exact power of two g_i so that ||g_i k_i|| is in (0.5, 1];
-//    x = dot * r_j + 3 then lies in [2, 4), where the fp32 bit pattern is monotone and the
-//    low mantissa bits can carry a column code: one v_max_u32 reduces value and argmax
-//    together.  With a running update per chunk the code is the register slot (4 bits,
-//    quantum 2^-18 of the scaled similarity); with one per tile of 4 chunks it also holds
-//    the chunk's place in the tile (6 bits, quantum 2^-16), so the compare-and-select of the
-//    running maximum runs once per tile instead of once per chunk.  Either quantum is far
-//    below the 1e-3 tolerance.  The first chunk of the running maximum's chunk (or tile) is
-//    kept beside it.
+//  * A workgroup owns RB = 4 * NSUB * 32 consecutive slots (its stationary rows) and sweeps the
+//    columns from its own slots on to the end: the upper triangle of the pair matrix.  Each
+//    wave holds NSUB 32-row blocks as MFMA A operands in registers for the whole sweep (d <= 128
+//    makes this a short-K contraction); columns stream through double-buffered LDS tiles of
+//    TN = 32 * CPT slots, moved by direct global -> LDS loads, as MFMA B operands.
+//  * v_mfma_f32_32x32x16_bf16 gives each lane one column j (lane % 32) and 16 rows: register v
+//    holds row 8*(v/4) + 4*(lane/32) + v%4.
+//  * Both reductions work on x = dot * r' + 3 in [2, 4), where the fp32 bit pattern is monotone
+//    and the low bits can carry an index: for token t and candidate u, x = dot * r'_u + 3 (the
+//    similarity is (x - 3) * r'_t), whichever of the two is the row, so a pair's value has the
+//    same bits on both sides and the same pair is found whatever its place in the sweep.
+//     - column direction: max over a lane's 16 * NSUB rows, index = the register; one LDS
+//       64-bit max per 32 columns merges the waves, one global 64-bit max per column and tile
+//       merges the workgroups;
+//     - row direction: a running maximum per register (never reduced across lanes in the
+//       sweep), index = the 32-column chunk inside a window of 2^BITS chunks; at the end of a
+//       window the 32 lanes of a row are reduced and merged by one global 64-bit max per row.
+//    The 64-bit candidates order by value, then by the smaller slot (the smaller position inside
+//    its group), so results do not depend on the order of the merges.
+//  * Cost per pair of tokens: 5 VALU instructions per lane element (two v_fma, two v_and_or, two
+//    halves of a v_max3) beside half the MFMA work of a full square.  The sweep is bound by the VALU
+//    (75% busy at d = 128, 32k tokens); with every ordered pair on its own it was bound by the MFMA
+//    (1313 of the 1340 TFLOP/s a large matrix product reaches).
+//  * Measured, full square -> upper triangle, this kernel alone: 288 heads x 32k, d = 128
+//    60.3 -> 41.7 ms; 288 heads x 64 ragged sequences of 1k-4k 29.3 -> 24.7 ms; 8 heads x 4001
+//    101 -> 40 us; 128 heads x 8k, d = 64 1193 -> 1162 us (half the MFMA work per pair, the same
+//    VALU work); counting, 288 x 16k 14.7 -> 9.1 ms.  Two waves per SIMD: with one, nothing hides
+//    the row direction's serial maxima (NSUB 2 and 4, both slower); with three the 2 x 16 running
+//    maxima per row block do not fit.
 //  * Products of bf16 values are exact in fp32; accumulation is fp32.  fp32 keys use the
-//    split k = hi + lo (bf16 each) and the three products hi.hi + lo.hi + hi.lo, laid out
-//    as a contraction over 3d.
-//  * Pairs inside the window and padding columns only occur in a few chunks per wave, found
-//    by scalar range tests; the sweep drops their results and a masked pass redoes them at
-//    the end (with the tile merge, per 32-row block, and the padding of a group's last
-//    chunk holds copies of its last column, so that chunk is only redone when counting).
-//    All other chunks take a 2.5-instruction-per-element epilogue (v_fmaak, v_and_or, half
-//    a v_max3).
+//    split k = hi + lo (bf16 each) and the sums hi.hi + (lo.hi + hi.lo), the two cross sums
+//    in accumulators of their own: swapping the two tokens swaps them, and their sum is the
+//    same.
+//  * Chunks that hold pairs inside the window, the rows' own chunks and padding are dropped by
+//    scalar masks in the sweep (their r' and the bias become 0, so x stays below any candidate);
+//    a masked pass after the sweep redoes those that hold real pairs, with the window tested per
+//    element (a kernel of its own for them was bound by load latency: 5.6 ms of the ragged batch).
+//  * Few row blocks leave the chip idle: a row block's columns are then cut into up to 16 segments,
+//    one workgroup each, until 1024 workgroups are in flight (4 per CU: the segments near the end
+//    of the triangle are short).  The candidates merge them like any other workgroups.
+//  * The S0 columns alone (no best_all) are swept by the kernel in sim_retained.hip: the lower half
+//    of a rectangle of S0 x all cannot be shared.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
 
-#include "../twinkv_internal.h"
+#include "sim_common.h"
 
 namespace twinkv {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned long long u64;
 
-template <int D, bool SPLIT, int NSUB, int NWAVES, int CPT, int OCC, int FG>
+constexpr uint32_t kBias = 0x40400000u;  // 3.0f
+
+template <int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC_>
 struct Cfg {
-  static_assert(FG == 1 || FG == CPT, "results merge per chunk or per tile");
-  static constexpr int WG_PER_CU = OCC * 4 / NWAVES;  // OCC waves per SIMD
-  // count mode's epilogue holds more registers: at most 2 waves per SIMD
-  static constexpr int WG_PER_CU_COUNT = (OCC < 2 ? OCC : 2) * 4 / NWAVES;
-  static constexpr int KSTEPS = SPLIT ? 3 * D / 16 : D / 16;
+  static constexpr int OCC = OCC_;  // workgroups per CU (waves per SIMD)
+  // registers of the last row block whose even chunks' candidates wait for the odd chunk's
+  static constexpr int HOLD_LAST = D != 128 ? 16 : (SPLIT ? 0 : 8);
   static constexpr int DCOL = SPLIT ? 2 * D : D;      // bf16 elements per column in LDS
+  static constexpr int UF = DCOL / 16;                // fragments of one key
+  static constexpr int MFMAS = SPLIT ? 3 * D / 16 : D / 16;
   static constexpr int PPC = DCOL / 8;                // 16-byte pieces per column
-  static constexpr int SWZ = (PPC < 16 ? PPC : 16) - 1;  // piece-index XOR swizzle mask
-  // columns sharing one 256-byte LDS bank row (2 at d = 64 bf16), and the period in
-  // columns of the swizzle ((column / CPR) & SWZ)
-  static constexpr int CPR = DCOL * 2 < 256 ? 256 / (DCOL * 2) : 1;
-  static constexpr int SWZ_PERIOD = (SWZ + 1) * CPR;
-  static_assert(kChunk % SWZ_PERIOD == 0, "a chunk's columns repeat the swizzle");
   static constexpr int TN = CPT * kChunk;             // columns per LDS tile
-  static constexpr int NT = NWAVES * 64;
-  static constexpr int RB = NWAVES * NSUB * 32;       // rows per workgroup
+  static constexpr int NT = kWaves * 64;
+  static constexpr int WR = NSUB * 32;                // rows per wave
+  static constexpr int RB = kWaves * WR;              // rows per workgroup
   static constexpr int CHUNK_BYTES = kChunk * DCOL * 2;  // keys of one 32-column chunk
   static constexpr int KEY_BYTES = TN * DCOL * 2;
-  static constexpr int STAGE = KEY_BYTES + TN * 8;    // keys + inverse norms + positions
-  static constexpr int RETIRED = NWAVES * NSUB * 64 * 8;  // S0 results parked in LDS
-  static constexpr int LOADS_PER_WAVE = TN * PPC / (NWAVES * 64);  // 1-KB direct loads
-  // VALU instructions the schedule places beside each MFMA: one chunk's epilogue (about 40
-  // with the tile merge, 48 with a running update per chunk) over its KSTEPS MFMAs
-  static constexpr int VALU_PER_MFMA = ((FG > 1 ? 40 : 48) + KSTEPS - 1) / KSTEPS;
-  static_assert((TN * PPC) % (NWAVES * 64) == 0, "tile copy must divide evenly");
-  static_assert(TN % 64 == 0, "the column tables move in 64-column (256-byte) pieces");
-  static_assert(2 * (KEY_BYTES + TN * 8) + RETIRED <= 160 * 1024 / WG_PER_CU,
-                "LDS of WG_PER_CU workgroups must fit one CU");
-};
-
-// Element offset of k-step t inside a column (A operand) / a row (B operand).
-// bf16 keys: plain. fp32 keys: columns hold [hi | lo], rows hold [hi | lo]; the three
-// k-step groups pair (col hi, row hi), (col lo, row hi), (col hi, row lo).
-template <int D, bool SPLIT>
-__device__ constexpr int col_off(int t) {
-  if constexpr (!SPLIT) {
-    return t * 16;
-  } else {
-    constexpr int G = D / 16;
-    return t < G ? t * 16 : (t < 2 * G ? D + (t - G) * 16 : (t - 2 * G) * 16);
-  }
-}
-template <int D, bool SPLIT>
-__device__ constexpr int row_off(int t) {
-  if constexpr (!SPLIT) {
-    return t * 16;
-  } else {
-    constexpr int G = D / 16;
-    return t < G ? t * 16 : (t < 2 * G ? (t - G) * 16 : D + (t - 2 * G) * 16);
-  }
-}
-
-// Power of two g with ||g k|| in (0.5, 1] given r = 1/||k|| (1 for zero or bad keys).
-__device__ inline float row_scale(float r) {
-  if (!(r > 0.0f) || !(r < 3.0e38f)) return 1.0f;
-  int e;
-  (void)frexpf(r, &e);
-  return ldexpf(1.0f, e - 1);
-}
-
-// Multiply 8 bf16 values by a power of two.  Exact unless a value leaves the normal range.
-__device__ inline bf16x8 scale8(uint4 raw, float g) {
-  uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-  uint32_t o[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const float lo = __uint_as_float(w[k] << 16) * g;
-    const float hi = __uint_as_float(w[k] & 0xFFFF0000u) * g;
-    o[k] = (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xFFFF0000u);
-  }
-  uint4 r = make_uint4(o[0], o[1], o[2], o[3]);
-  return __builtin_bit_cast(bf16x8, r);
-}
-
-// Column (0..31 inside a chunk) held by register v of a lane in half `half`.
-__device__ inline int slot_col(int v, int half) { return 8 * (v >> 2) + 4 * half + (v & 3); }
-
-constexpr uint32_t kValidMin = 0x3F800000u;  // packed values >= 1.0f are real candidates
-
-// Longest sequence whose row keys the similarity sweep reads from the partitioned column copy.
-constexpr int kRowsFromCopyMaxLen = 8192;
-
-// Fourth dword of a raw buffer resource on gfx9-family parts (32-bit data format).
-constexpr int kBufferFlags = 0x00020000;
-
-// BYTES (4 or 16) per lane from base + voff straight into LDS at lds + BYTES * lane, through
-// a raw buffer resource of nbytes: lanes whose offset is past the end read nothing (zeros).
-__device__ inline void load_block_lds16(const void* base, int nbytes, int voff, char* lds) {
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, nbytes, kBufferFlags);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (void __attribute__((address_space(3)))*)lds, 16,
-                                           voff, 0, 0, 0);
-}
-__device__ inline void load_block_lds4(const void* base, int nbytes, int voff, char* lds) {
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, nbytes, kBufferFlags);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (void __attribute__((address_space(3)))*)lds, 4,
-                                           voff, 0, 0, 0);
-}
-
-// Scheduling-group masks for __builtin_amdgcn_sched_group_barrier.
-constexpr int kSchedValu = 0x002;
-constexpr int kSchedMfma = 0x008;
-constexpr int kSchedDsRead = 0x100;
-
-// Low bits of a packed candidate when the chunks of a group of FG chunks are merged before
-// the running update: register slot v (4 bits) and the chunk's place kc in the group,
-// coded as LOW - (16 kc + v), so that among equal values the smaller column has the larger
-// code.  FG = 1 leaves the plain slot code 15 - v.
-template <int FG>
-struct Slots {
-  static_assert(FG == 1 || FG == 2 || FG == 4, "1, 2 or 4 chunks per group");
-  static constexpr int BITS = 4 + (FG >= 2) + (FG >= 4);
+  static constexpr int STAGE = KEY_BYTES + TN * 4;    // keys + r'
+  static constexpr int COL_BYTES = 3 * 2 * TN * 8;    // column candidates of three tiles
+  static constexpr int LDS_BYTES = 2 * STAGE + COL_BYTES + RB * 4;
+  static constexpr int LOADS_PER_WAVE = TN * PPC / (kWaves * 64);  // 1-KB direct loads
   static constexpr uint32_t LOW = (1u << BITS) - 1u;
+  static constexpr int WIN = 1 << BITS;               // chunks per window of the row direction
+  static_assert(WIN % CPT == 0 && (CPT % 2) == 0, "whole tiles per window, chunks in pairs");
+  static_assert(RB % TN == 0, "a workgroup's rows start on a tile boundary");
+  static_assert(kGroupAlign % TN == 0, "the evicted group must start on a tile boundary");
+  static_assert(kGroupAlign % WR == 0, "a wave's rows lie in one group");
+  static_assert((TN * PPC) % (kWaves * 64) == 0, "tile copy must divide evenly");
+  static_assert(TN % 64 == 0 && TN <= 128, "the r' table moves in 64-column pieces");
+  static_assert(LDS_BYTES * OCC <= 160 * 1024, "LDS of OCC workgroups must fit one CU");
 };
 
-// Value + code of the best column of one lane's 16 accumulators of chunk kc of its group.
-template <int FG>
-__device__ inline uint32_t chunk_best(const f32x16& acc, const float (&rv)[16], int kc) {
-  constexpr uint32_t LOW = Slots<FG>::LOW;
-  uint32_t b = 0u;
+__device__ inline void max_global(u64* p, u64 v) {
+  (void)__hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// LDS maximum / sum without a result, as instructions of their own: the compiler would wait for
+// every direct global -> LDS load in flight before an LDS atomic of its own.  The waits before
+// the barriers that publish them are explicit (finish_tile).
+__device__ inline uint32_t lds_offset(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+__device__ inline void max_lds(uint32_t off, u64 v) {
+  asm volatile("ds_max_u64 %0, %1" : : "v"(off), "v"(v) : "memory");
+}
+__device__ inline void add_lds(uint32_t off, uint32_t v) {
+  asm volatile("ds_add_u32 %0, %1" : : "v"(off), "v"(v) : "memory");
+}
+
+// x of the lane whose index differs by the DPP control: quad_perm xor 1 / xor 2, mirror inside
+// 8 lanes (xor 7), rotate by 8 inside 16 lanes (xor 8).
+template <int CTRL>
+__device__ inline uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor7 = 0x141, kXor8 = 0x128;
+
+// One step of the row reduction over lanes: each lane keeps one of two registers (bit clear:
+// a, set: b) and merges its partner's copy of it.
+template <int CTRL>
+__device__ inline u64 max_step(u64 a, u64 b, bool bit) {
+  const u64 keep = bit ? b : a, send = bit ? a : b;
+  const u64 got = ((u64)dpp<CTRL>((uint32_t)(send >> 32)) << 32) | dpp<CTRL>((uint32_t)send);
+  return keep > got ? keep : got;
+}
+template <int CTRL>
+__device__ inline uint32_t sum_step(uint32_t a, uint32_t b, bool bit) {
+  const uint32_t keep = bit ? b : a, send = bit ? a : b;
+  return keep + dpp<CTRL>(send);
+}
+
+// Which register's row a lane holds after the lane reductions below.
+__device__ inline int reduced_reg(int l32) {
+  return ((l32 >> 4) << 3) | (((l32 >> 3) & 1) << 2) | (((l32 >> 2) & 1) << 1) | ((l32 >> 1) & 1);
+}
+
+// The largest (value, then smaller lane) of each of 16 registers over the 32 lanes of a half:
+// the lane pair 2m, 2m + 1 ends with register reduced_reg's result as value << 32 | 31 - lane.
+__device__ inline u64 reduce_rows_max(const uint32_t (&run)[16], int l32) {
+  u64 k8[8];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const float x = fmaf(acc[v], rv[v], 3.0f);
-    b = max(b, (__float_as_uint(x) & ~LOW) | (LOW - (uint32_t)(16 * kc + v)));
+  for (int i = 0; i < 8; ++i) {
+    // lanes 0-15 take register i, lanes 16-31 register i + 8
+    const auto sw = __builtin_amdgcn_permlane16_swap(run[i], run[i + 8], false, false);
+    const uint32_t lo = sw[0], hi = sw[1];  // from lanes 0-15 / 16-31 of the half
+    const bool up = hi > lo;
+    k8[i] = ((u64)(up ? hi : lo) << 32) | (uint32_t)(31 - ((l32 & 15) + (up ? 16 : 0)));
   }
-  return b;
-}
-
-// Number of a lane's 16 similarities above the row's threshold (count mode, Eq. 2):
-// y = dot * r_j + c_i with c_i = -tau * g_i / r_i is positive exactly when sim(i, j) > tau
-// (a y of exactly +0, sim equal to tau up to fp32 rounding, counts as above).  Each sign
-// bit is shifted into a mask with one v_alignbit (a serial chain the compiler cannot
-// reassociate into a wide tree), and one v_bcnt counts them.
-__device__ inline uint32_t chunk_count(const f32x16& acc, const float (&rv)[16], float c_row) {
-  uint32_t neg = 0u;
+  u64 k4[4], k2[2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v)
-    neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(fmaf(acc[v], rv[v], c_row)), 31);
-  return 16u - (uint32_t)__builtin_popcount(neg);
+  for (int i = 0; i < 4; ++i) k4[i] = max_step<kXor8>(k8[i], k8[i + 4], (l32 & 8) != 0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) k2[i] = max_step<kXor7>(k4[i], k4[i + 2], (l32 & 4) != 0);
+  const u64 k1 = max_step<kXor2>(k2[0], k2[1], (l32 & 2) != 0);
+  const u64 got = ((u64)dpp<kXor1>((uint32_t)(k1 >> 32)) << 32) | dpp<kXor1>((uint32_t)k1);
+  return k1 > got ? k1 : got;
+}
+// The sums of 16 registers over the 32 lanes of a half, in the same places.
+__device__ inline uint32_t reduce_rows_sum(const uint32_t (&c)[16], int l32) {
+  uint32_t k8[8], k4[4], k2[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(c[i], c[i + 8], false, false);
+    k8[i] = sw[0] + sw[1];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) k4[i] = sum_step<kXor8>(k8[i], k8[i + 4], (l32 & 8) != 0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) k2[i] = sum_step<kXor7>(k4[i], k4[i + 2], (l32 & 4) != 0);
+  const uint32_t k1 = sum_step<kXor2>(k2[0], k2[1], (l32 & 2) != 0);
+  return k1 + dpp<kXor1>(k1);
 }
 
-// Branch-free running update: a strictly larger value (code bits ignored) replaces the
-// running best, so an earlier chunk (group) keeps exact ties.  c: its first chunk.
-template <int FG>
-__device__ inline void run_update(uint32_t best, int c, uint32_t& run, int& cid) {
-  constexpr int B = Slots<FG>::BITS;
-  const bool upd = (best >> B) > (run >> B);
-  run = upd ? best : run;
-  cid = upd ? c : cid;
-}
-
-// A running best in the per-chunk form: value, slot code 15 - v, chunk index.
-template <int FG>
-__device__ inline void to_chunk_form(uint32_t& run, int& cid) {
-  constexpr uint32_t LOW = Slots<FG>::LOW;
-  const uint32_t q = LOW - (run & LOW);
-  cid += (int)(q >> 4);
-  run = (run & ~LOW) | (15u - (q & 15u));
-}
-
-template <int D, bool SPLIT, int NSUB, int NWAVES, int CPT, int OCC, int FG, bool COUNT>
-__global__ __launch_bounds__(NWAVES * 64,
-                             (COUNT ? Cfg<D, SPLIT, NSUB, NWAVES, CPT, OCC, FG>::WG_PER_CU_COUNT
-                                    : Cfg<D, SPLIT, NSUB, NWAVES, CPT, OCC, FG>::WG_PER_CU))
-void sim_reduce_kernel(SimArgs a) {
-  using C = Cfg<D, SPLIT, NSUB, NWAVES, CPT, OCC, FG>;
-  constexpr uint32_t LOW = Slots<FG>::LOW;
-  static_assert(kGroupAlign % C::TN == 0, "the evicted group must start on a tile boundary");
-  __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE + C::RETIRED];
-
-  // ---- which (head, sequence, row block) this workgroup owns --------------------------
-  // With >= 8 heads, heads h = x (mod 8) go to the XCD x the hardware dispatches block
-  // b = x (mod 8) to, so one problem's row blocks share that XCD's L2; inside an XCD the
-  // sequences run longest first.
-  int k, hx, h0, hstep;
-  if (a.n_heads >= 8) {
-    const int x = blockIdx.x & 7;
-    k = blockIdx.x >> 3;
-    hx = (a.n_heads - x + 7) >> 3;
-    h0 = x;
-    hstep = 8;
+// Column chunks with pairs inside the window of a wave's rows (slots [row0, row0 + rows) of group
+// grp, at least one of them real): in the rows' own group up to a_hi, in the other group [b_lo, b_hi].  The columns at positions x0 <= j < x1 are one contiguous range of slots
+// per group, read off the S0 prefix counts.
+struct Band {
+  int a_hi, b_lo, b_hi;
+};
+__device__ inline Band window_band(const SimArgs& a, const Place& pl, int row0, int rows, int grp) {
+  const int32_t* pc = a.pcol + pl.colbase;
+  const int32_t* prk = a.prank + pl.colbase;
+  const int ret_pad = pl.ret_chunks * kChunk;
+  const int end = grp == 0 ? pl.n_ret : ret_pad + (pl.len - pl.n_ret);  // of the group's real slots
+  Band bd{-1, 1, 0};
+  const int x0 = max(pc[row0] - a.w, 0), x1 = min(pc[min(row0 + rows, end) - 1] + a.w + 1, pl.len);
+  const int r0 = prk[x0], r1 = prk[x1];
+  const int e0 = ret_pad + (x0 - r0), e1 = ret_pad + (x1 - r1);
+  if (grp == 0) {
+    bd.a_hi = (r1 - 1) / kChunk;
+    if (e1 > e0) {
+      bd.b_lo = e0 / kChunk;
+      bd.b_hi = (e1 - 1) / kChunk;
+    }
   } else {
-    k = blockIdx.x;
-    hx = a.n_heads;
-    h0 = 0;
-    hstep = 1;
+    bd.a_hi = (e1 - 1) / kChunk;
   }
-  if (k >= hx * a.total_tiles) return;
-  int lo = 0, hi = a.n_seqs - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (hx * a.seqtab[mid].tile_cum <= k) lo = mid; else hi = mid - 1;
+  bd.a_hi = __builtin_amdgcn_readfirstlane(bd.a_hi);
+  bd.b_lo = __builtin_amdgcn_readfirstlane(bd.b_lo);
+  bd.b_hi = __builtin_amdgcn_readfirstlane(bd.b_hi);
+  return bd;
+}
+
+// Position of a slot of group grp; padding (copies of the group's last token) has that token's, so
+// that it stays an exact tie of it.
+__device__ inline int slot_position(const SimArgs& a, const Place& pl, int slot, int grp) {
+  const int last = grp == 0 ? pl.n_ret - 1 : pl.ret_chunks * kChunk + (pl.len - pl.n_ret) - 1;
+  return a.pcol[pl.colbase + min(slot, last)];
+}
+
+// The window test of a pair with the row at pi: base - pi >= thr as unsigned numbers.  In the rows'
+// own group (SAME) the column has to lie more than w after the row, so that each pair counts once
+// and the lower half of the triangle not at all; in the other group more than w away on either side.
+struct Window {
+  uint32_t base, thr;
+};
+__device__ inline Window window_of(int pj, int w, bool same) {
+  return same ? Window{(uint32_t)(pj - w - 1) + 0x80000000u, 0x80000000u}
+              : Window{(uint32_t)(pj + w), 2u * (uint32_t)w + 1u};
+}
+
+// A 32-row block's MFMA A operands and r' (count mode: thresholds) of a lane's 16 rows.  A block
+// past the last slot reads the last one; its results are never used.
+template <bool COUNT, int D, bool SPLIT, int UF>
+__device__ inline void load_rows(const SimArgs& a, const Place& pl, int row0, int l32, int half,
+                                 bf16x8 (&af)[UF], float (&rs)[16]) {
+  constexpr int DCOL = SPLIT ? 2 * D : D;
+  const int r0 = min(row0, pl.total_chunks * kChunk - 32);
+  const uint16_t* src = a.pkeys + (pl.colbase + r0) * DCOL + 8 * (l32 + 32 * half);
+#pragma unroll
+  for (int t = 0; t < UF; ++t) af[t] = *reinterpret_cast<const bf16x8*>(src + 512 * t);
+  const float* rc = a.rcol + pl.colbase + r0 + 4 * half;
+#pragma unroll
+  for (int v4 = 0; v4 < 4; ++v4) {
+    const float4 x = *reinterpret_cast<const float4*>(rc + 8 * v4);
+    rs[4 * v4 + 0] = x.x;
+    rs[4 * v4 + 1] = x.y;
+    rs[4 * v4 + 2] = x.z;
+    rs[4 * v4 + 3] = x.w;
   }
-  const int nb = a.seqtab[lo].nb;
-  const int local = k - hx * a.seqtab[lo].tile_cum;
-  const int head = h0 + hstep * (local / nb);
-  const int rb = local - (local / nb) * nb;
-  const int seq = a.seqtab[lo].sorted_seq;
-  const SeqInfo si = a.seqtab[seq];
-  const int q = head * a.n_seqs + seq;
-  const ProblemMeta pm = a.pmeta[q];
-  const int len = si.len;
-  const int nchunks = a.want_all ? pm.total_chunks : pm.ret_chunks;
-  const int ret_chunks = pm.ret_chunks;                      // a multiple of CPT
-  const int ret_real = (pm.n_ret + kChunk - 1) / kChunk;     // S0 chunks with a real column
-  const int ncols = nchunks * kChunk;
+  if constexpr (COUNT) {
+    // sim(i, j) > tau  <=>  dot * r'_j - tau / r'_i > 0.  A zero key has similarity 0 to every
+    // key: it counts every candidate exactly when tau < 0 (the smallest normal number stands
+    // for tau = 0, so that a similarity of exactly 0 is not above it).  Rows that are padding
+    // count nothing.
+    const float t = a.tau == 0.0f ? 1.17549435e-38f : a.tau;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float r = rs[v];
+      const bool real = row0 + slot_row(v, half) < pl.len;
+      rs[v] = !real ? -INFINITY : (r > 0.0f ? -t / r : (a.tau < 0.0f ? INFINITY : -INFINITY));
+    }
+  }
+}
+
+template <bool COUNT, int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC>
+__global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a, int nseg) {
+  using C = Cfg<D, SPLIT, NSUB, CPT, BITS, OCC>;
+  constexpr uint32_t LOW = C::LOW;
+  constexpr int G = D / 16;
+  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+  // column candidates (counts in count mode) of three tiles in turn, one plane per group of
+  // the rows they came from: [tile % 3][group][column]
+  u64* const s_col = reinterpret_cast<u64*>(smem + 2 * C::STAGE);
+  int* const s_pos = reinterpret_cast<int*>(smem + 2 * C::STAGE + C::COL_BYTES);  // the rows' positions
+
+  Place pl;
+  int seg;  // segment of the row block's columns
+  if (!find_place(a, (int)blockIdx.x, pl, seg)) return;
+  const int nslots = pl.total_chunks * kChunk;
+  const int ret_chunks = pl.ret_chunks;                      // a multiple of kGroupAlign / 32
+  const int ret_pad = ret_chunks * kChunk;
+  // (the row blocks are counted for the largest padding)
+  if (pl.rb * C::RB >= nslots) return;
+  const int ret_real = (pl.n_ret + kChunk - 1) / kChunk;     // S0 chunks with a real column
+  const int nchunks = pl.total_chunks;
+  const int ncols = nchunks * kChunk;                        // columns swept
   const int ntiles = (nchunks + CPT - 1) / CPT;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint2* retired = reinterpret_cast<uint2*>(smem + 2 * C::STAGE) + wave * NSUB * 64;
   const int lane = threadIdx.x & 63;
   const int half = lane >> 5;
   const int l32 = lane & 31;
-  const int wrow0 = rb * C::RB + wave * NSUB * 32;
+  const int row0 = pl.rb * C::RB + wave * C::WR;  // this wave's first slot
+  const int grp = row0 >= ret_pad ? 1 : 0;        // ... and its group (0: S0, 1: evicted)
 
-  const int64_t colbase = (int64_t)head * a.PT + si.perm_off;
-  const uint16_t* kb = (const uint16_t*)a.keys + (int64_t)head * a.head_stride +
-                       (int64_t)si.start * a.token_stride;
-  const uint16_t* pk = a.pkeys + colbase * C::DCOL;
-  const int32_t* pc = a.pcol + colbase;
-  const float* rc = a.rcol + colbase;
-  const float* rinv = a.rinv + (int64_t)head * a.T + si.start;
+  const uint16_t* pk = a.pkeys + pl.colbase * C::DCOL;
+  const float* rc = a.rcol + pl.colbase;
+  const int64_t plane = (int64_t)a.n_heads * a.PT;
+  u64* const best0 = COUNT ? nullptr : reinterpret_cast<u64*>(a.best) + pl.colbase;
+  int32_t* const counts = COUNT ? a.counts + pl.rowbase : nullptr;
 
-  // ---- chunks that need the masked epilogue: the window band of this wave's rows and the
-  // partly padded last chunk of each group.  In the [S0 | evicted] order the columns j with
-  // x0 <= j < x1 occupy one contiguous range per group, read off the S0 prefix counts.
-  int cr_lo, cr_hi, ce_lo, ce_hi, pad_r, pad_e;
-  {
-    const int32_t* prk = a.prank + colbase;
-    const int x0 = min(max(wrow0 - a.w, 0), len);
-    const int x1 = min(max(wrow0 + NSUB * 32 + a.w, 0), len);
-    const int r0 = prk[x0], r1 = prk[x1];
-    const int ret_pad = ret_chunks * kChunk;
-    const int e0 = ret_pad + (x0 - r0), e1 = ret_pad + (x1 - r1);
-    cr_lo = r0 < r1 ? r0 / kChunk : 1;
-    cr_hi = r0 < r1 ? (r1 - 1) / kChunk : 0;
-    ce_lo = e0 < e1 ? e0 / kChunk : 1;
-    ce_hi = e0 < e1 ? (e1 - 1) / kChunk : 0;
-    const int n_ev = len - pm.n_ret;
-    pad_r = (pm.n_ret % kChunk) ? pm.n_ret / kChunk : -1;
-    pad_e = (n_ev % kChunk) ? (ret_pad + n_ev) / kChunk : -1;
-    if constexpr (!COUNT && FG > 1) {
-      // the key preparation fills a group's partial last chunk with copies of its last
-      // column (exact ties), so the maximum needs no padding test there; counting does,
-      // and the per-chunk configurations keep the test (it is still correct: the masked
-      // pass skips the copies by their position -1)
-      pad_r = -1;
-      pad_e = -1;
-    }
-    cr_lo = __builtin_amdgcn_readfirstlane(cr_lo);
-    cr_hi = __builtin_amdgcn_readfirstlane(cr_hi);
-    ce_lo = __builtin_amdgcn_readfirstlane(ce_lo);
-    ce_hi = __builtin_amdgcn_readfirstlane(ce_hi);
-    pad_r = __builtin_amdgcn_readfirstlane(pad_r);
-    pad_e = __builtin_amdgcn_readfirstlane(pad_e);
-  }
-  // With the tile merge, the band is also kept per 32-row block: a chunk is dropped and
-  // redone only for the row blocks whose own band holds it (the sweep's chunk mask is one
-  // scalar operand per chunk and row block either way).
-  constexpr bool SUB_BANDS = FG > 1;
-  int sr_lo[NSUB], sr_hi[NSUB], se_lo[NSUB], se_hi[NSUB];
-  if constexpr (SUB_BANDS) {
-    const int32_t* prk = a.prank + colbase;
-    const int ret_pad = ret_chunks * kChunk;
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) {
-      const int x0 = min(max(wrow0 + 32 * s - a.w, 0), len);
-      const int x1 = min(max(wrow0 + 32 * s + 32 + a.w, 0), len);
-      const int r0 = prk[x0], r1 = prk[x1];
-      const int e0 = ret_pad + (x0 - r0), e1 = ret_pad + (x1 - r1);
-      sr_lo[s] = __builtin_amdgcn_readfirstlane(r0 < r1 ? r0 / kChunk : 1);
-      sr_hi[s] = __builtin_amdgcn_readfirstlane(r0 < r1 ? (r1 - 1) / kChunk : 0);
-      se_lo[s] = __builtin_amdgcn_readfirstlane(e0 < e1 ? e0 / kChunk : 1);
-      se_hi[s] = __builtin_amdgcn_readfirstlane(e0 < e1 ? (e1 - 1) / kChunk : 0);
-    }
-  }
-  // Result bits of the CPT chunks of a tile in the main sweep (bit k: keep chunk c0 + k).
-  // Dropped: chunks the masked pass redoes, the padding-only chunks that align the S0 group,
-  // and chunks past the last one.  Branch-free scalar arithmetic, so the tile body stays
-  // one straight-line block.
+  // A wave without rows of its own here only takes its share of the tile loads.
+  const bool active = row0 < nslots && !(row0 >= pl.n_ret && row0 < ret_pad);
+
+  // ---- chunks the sweep drops for this wave: up to bd.a_hi (its own, their window band and the
+  // other half of the triangle) and the band in the other group, which the pass after the sweep
+  // redoes, and padding.  Count mode: copies of the last column must not be counted, so the
+  // partly filled last chunk is redone too (there is no S0 group then).
+  Band bd{-1, 1, 0};
+  if (active) bd = window_band(a, pl, row0, C::WR, grp);
+  const int pad_c = COUNT && (pl.len % kChunk) ? pl.total_chunks - 1 : -1;
+  // Result bits of a tile in the sweep (bit k: chunk c0 + k counts).
   auto keep_bits = [&](int c0) -> uint32_t {
     // most tiles drop nothing: one range test over the whole tile
     const int c1 = c0 + CPT - 1;
-    const bool clean = (c1 < nchunks) && !(c1 >= ret_real && c0 < ret_chunks) &&
-                       !(c1 >= cr_lo && c0 <= cr_hi) && !(c1 >= ce_lo && c0 <= ce_hi) &&
-                       !(pad_r >= c0 && pad_r <= c1) && !(pad_e >= c0 && pad_e <= c1);
-    if (clean) return SUB_BANDS ? (1u << (CPT * NSUB)) - 1u : (1u << CPT) - 1u;
+    if (c0 > bd.a_hi && c1 < nchunks && !(c1 >= ret_real && c0 < ret_chunks) &&
+        !(c1 >= bd.b_lo && c0 <= bd.b_hi) && !(pad_c >= c0 && pad_c <= c1))
+      return (1u << CPT) - 1u;
     uint32_t bits = 0u;
-    if constexpr (SUB_BANDS) {
-#pragma unroll
-      for (int kc = 0; kc < CPT; ++kc) {
-        const int gc = c0 + kc;
-        const int common = (int)(gc >= nchunks) |
-                           ((int)(gc >= ret_real) & (int)(gc < ret_chunks)) |
-                           (int)(gc == pad_r) | (int)(gc == pad_e);
-#pragma unroll
-        for (int sb = 0; sb < NSUB; ++sb) {
-          const int drop = common | ((int)(gc >= sr_lo[sb]) & (int)(gc <= sr_hi[sb])) |
-                           ((int)(gc >= se_lo[sb]) & (int)(gc <= se_hi[sb]));
-          bits |= (uint32_t)(drop ^ 1) << (kc * NSUB + sb);
-        }
-      }
-      return bits;
-    }
 #pragma unroll
     for (int kc = 0; kc < CPT; ++kc) {
       const int gc = c0 + kc;
-      const int drop = (int)(gc >= nchunks) | ((int)(gc >= ret_real) & (int)(gc < ret_chunks)) |
-                       ((int)(gc >= cr_lo) & (int)(gc <= cr_hi)) |
-                       ((int)(gc >= ce_lo) & (int)(gc <= ce_hi)) | (int)(gc == pad_r) |
-                       (int)(gc == pad_e);
+      const int drop = (int)(gc <= bd.a_hi) | (int)(gc >= nchunks) |
+                       ((int)(gc >= ret_real) & (int)(gc < ret_chunks)) |
+                       ((int)(gc >= bd.b_lo) & (int)(gc <= bd.b_hi)) | (int)(gc == pad_c);
       bits |= (uint32_t)(drop ^ 1) << kc;
     }
     return bits;
   };
 
-  // ---- row keys: MFMA B operands, resident for the whole sweep ------------------------
-  bf16x8 bfrag[NSUB][C::KSTEPS];
-  // Count mode: sim(i, j) > tau  <=>  dot * r_j - tau * g_i / r_i > 0  (per row; a zero key
-  // has similarity 0 to every key, so it counts every candidate exactly when tau < 0).
-  float thr[NSUB];
+  // ---- this workgroup's tiles: from its own rows on, cut into nseg segments ----
+  int ta, tb;
   {
-    // All of a wave's row loads are issued before any of them is used (one memory round
-    // trip).  A row past the end of the sequence reads the last row instead: the results of
-    // its lane are never written.
-    // With every column copied (all-keys sweeps) and a short sequence, row i is read from its
-    // own column in the partitioned copy, which the problem's other row blocks are streaming
-    // through this XCD's L2, rather than from the key rows: the same bits, and no fresh lines
-    // pushed into L2 (measured about 1% faster on 1k-4k-token sequences, 0.2-0.5% slower at
-    // 16k-32k tokens, where the row keys are a small part of the traffic).
-    float ri[NSUB];
-    const uint16_t* src[NSUB];
-    if (!COUNT && a.want_all && len <= kRowsFromCopyMaxLen) {
-      const int32_t* prk = a.prank + colbase;
+    const int t0 = pl.rb * C::RB / C::TN;
+    const int per = (max(ntiles - t0, 0) + nseg - 1) / nseg;
+    ta = t0 + seg * per;
+    tb = min(ta + per, ntiles);
+  }
+
+  // ---- row keys: MFMA A operands, resident for the whole sweep --------------------------
+  // rs: r' of the lane's 16 * NSUB rows (count mode: their thresholds)
+  bf16x8 afrag[NSUB][C::UF];
+  float rs[NSUB][16];
+  if (active) {
 #pragma unroll
-      for (int s = 0; s < NSUB; ++s) {
-        const int i = min(wrow0 + s * 32 + l32, len - 1);
-        const int r0 = prk[i], r1 = prk[i + 1];
-        const int col = r1 > r0 ? r0 : ret_chunks * kChunk + (i - r0);
-        src[s] = pk + (int64_t)col * C::DCOL;
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < NSUB; ++s) {
-        const int i = min(wrow0 + s * 32 + l32, len - 1);
-        src[s] = kb + (int64_t)i * a.token_stride;
-      }
-    }
+    for (int s = 0; s < NSUB; ++s)
+      load_rows<COUNT, D, SPLIT, C::UF>(a, pl, row0 + 32 * s, l32, half, afrag[s], rs[s]);
+  } else {
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) {
-      const int i = min(wrow0 + s * 32 + l32, len - 1);
-      ri[s] = rinv[i];
 #pragma unroll
-      for (int t = 0; t < C::KSTEPS; ++t)
-        bfrag[s][t] = *reinterpret_cast<const bf16x8*>(src[s] + row_off<D, SPLIT>(t) + half * 8);
-    }
+      for (int t = 0; t < C::UF; ++t) afrag[s][t] = bf16x8{};
 #pragma unroll
-    for (int s = 0; s < NSUB; ++s) {
-      const float g = row_scale(ri[s]);
-      thr[s] = ri[s] > 0.0f ? -a.tau * g / ri[s] : (a.tau < 0.0f ? INFINITY : -INFINITY);
-#pragma unroll
-      for (int t = 0; t < C::KSTEPS; ++t)
-        bfrag[s][t] = scale8(__builtin_bit_cast(uint4, bfrag[s][t]), g);
+      for (int v = 0; v < 16; ++v) rs[s][v] = 0.0f;
     }
   }
 
-  // One running maximum per row block: S0 columns are swept first, and their results are
-  // parked in LDS (``retire``) when the sweep reaches the evicted columns.
-  // tb: with FG = CPT, the best of the current tile's chunks so far.
-  uint32_t run[NSUB], tb[NSUB];
-  int cid[NSUB];
+  // Row direction.  run: the running maximum of each register over the chunks of the current
+  // window, as value bits with LOW - (chunk - window) in the low bits; hold: the even chunk's
+  // candidates, merged with the odd chunk's by one v_max3 (where registers allow).  Count mode:
+  // run holds the sign bits of the last 32 chunks (newest in bit 0), kept which of those chunks
+  // count, and cnt the counts of the windows before, four rows of 8 bits a register (a lane
+  // counts at most one column per chunk; they are written out every 224 chunks).
+  uint32_t run[NSUB][16], hold[NSUB][16];
+  uint32_t cnt[NSUB][4];
+  uint32_t kept[NSUB];
 #pragma unroll
   for (int s = 0; s < NSUB; ++s) {
-    run[s] = 0u;
-    tb[s] = 0u;
-    cid[s] = 0;
-  }
-  bool retired_done = false;
-  auto retire = [&]() {
+    kept[s] = 0u;
 #pragma unroll
-    for (int s = 0; s < NSUB; ++s) {
-      if constexpr (!COUNT) to_chunk_form<FG>(run[s], cid[s]);
-      retired[s * 64 + lane] = make_uint2(run[s], (uint32_t)cid[s]);
-      run[s] = 0u;
-      cid[s] = 0;
+    for (int v = 0; v < 16; ++v) {
+      run[s][v] = hold[s][v] = 0u;
+      cnt[s][v / 4] = 0u;
     }
-    retired_done = true;
-  };
-
-  // ---- LDS addressing ------------------------------------------------------------------
-  // A column's 16-byte piece p is stored in slot p ^ ((column / CPR) & SWZ) of its row, so
-  // the lanes that read one piece of consecutive columns in one LDS pass hit distinct banks
-  // (with two 128-byte columns per 256-byte bank row at d = 64, the even and the odd columns
-  // take the two halves of the row and the swizzle changes every second column).  The
-  // swizzle repeats every SWZ_PERIOD columns, which divides 32, so for column c*32 + l32 it
-  // only depends on l32: the byte offset of k-step t of a lane's column is a lane constant
-  // plus c * (chunk bytes) plus the stage offset.
-  int aoff[C::KSTEPS];
-#pragma unroll
-  for (int t = 0; t < C::KSTEPS; ++t) {
-    const int part = (col_off<D, SPLIT>(t) >> 3) + half;
-    aoff[t] = l32 * (C::DCOL * 2) + ((part ^ ((l32 / C::CPR) & C::SWZ)) << 4);
   }
-  const int roff = C::KEY_BYTES + 16 * half;  // this lane's inverse norms inside a chunk
-
-  auto load_rv = [&](const char* st, int c, float (&rv)[16]) {
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      const float4 x = *reinterpret_cast<const float4*>(st + roff + c * kChunk * 4 + 32 * g4);
-      rv[4 * g4 + 0] = x.x;
-      rv[4 * g4 + 1] = x.y;
-      rv[4 * g4 + 2] = x.z;
-      rv[4 * g4 + 3] = x.w;
-    }
-  };
 
   // ---- column tiles: global -> LDS by direct (asynchronous) loads, double buffered ------
-  // Each wave moves LOADS_PER_WAVE blocks of 1 KB with buffer loads; lane l of a block lands
-  // at byte 16*l.  Block blk holds columns blk*B .. blk*B+B-1 (B = 64 / PPC), lane l piece
-  // l % PPC of column blk*B + l / PPC, stored in slot piece ^ ((column / CPR) & SWZ).  The
-  // buffer resource of a tile ends at the problem's last column, so the hardware range check
-  // turns loads past it into zeros instead of reads (those columns are never used).
-  constexpr int B = 64 / C::PPC;
-  constexpr int NV = C::SWZ_PERIOD / B;  // distinct lane offsets over a wave's blocks
-  static_assert(C::SWZ_PERIOD % B == 0 && ((C::LOADS_PER_WAVE * B) % C::SWZ_PERIOD) == 0,
-                "the swizzle of a block's columns must repeat with the block index");
-  const int lcol = lane / C::PPC;
-  int vlane[NV];
-#pragma unroll
-  for (int r = 0; r < NV; ++r)
-    vlane[r] = lcol * (C::DCOL * 2) + 16 * ((lane % C::PPC) ^ (((r * B + lcol) / C::CPR) & C::SWZ));
+  // The copy stores each 32-slot chunk piece by piece (16-byte piece p of the chunk's column c at
+  // p * 512 + 16 c), so a tile is one plain stream, a fragment read takes 64 consecutive 16-byte
+  // words (no bank conflicts) and every fragment lies at a constant offset from one lane address.
+  // Each wave moves LOADS_PER_WAVE blocks of 1 KB.  The buffer resource of a tile ends at the
+  // problem's last column, so the hardware range check turns loads past it into zeros instead of
+  // reads (those columns are dropped).
+  const uint32_t lane_base = lds_offset(smem) + 16 * lane;
+  auto read_frag = [&](uint32_t base, int t, int chunk) -> bf16x8 {
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(
+        (uintptr_t)(base + (uint32_t)(t * 1024 + chunk * C::CHUNK_BYTES)));
+  };
   auto issue_tile = [&](int tile, int buf) {
+    // one resource per tile (the range check sees a lane's offset and the instruction's; the
+    // instruction's offset also moves the LDS address, four 1-KB blocks per base)
     char* st = smem + buf * C::STAGE;
     const int64_t first = (int64_t)tile * C::TN;
     const int left = ncols - (int)first;                // > 0 for every issued tile
-    const int nbytes = (left < C::TN ? left : C::TN) * C::DCOL * 2;
+    const int ncol = left < C::TN ? left : C::TN;
+    const __amdgpu_buffer_rsrc_t rk = tile_rsrc(pk + first * C::DCOL, ncol * C::DCOL * 2);
+    const int base = wave * C::LOADS_PER_WAVE * 1024;
+    int ln = lane;
+    asm("" : "+v"(ln));  // (the offsets are made here: held over the sweep, they would be spilled)
 #pragma unroll
-    for (int kk = 0; kk < C::LOADS_PER_WAVE; ++kk) {
-      // one resource per 1-KB block, based at the block: the range check sees the whole
-      // offset of every lane
-      const int blk = wave * C::LOADS_PER_WAVE + kk;
-      const int rem = nbytes - blk * 1024;
-      load_block_lds16(pk + (first * C::DCOL + blk * 512), rem > 0 ? rem : 0,
-                       vlane[kk % NV], st + blk * 1024);
+    for (int kk = 0; kk < C::LOADS_PER_WAVE; kk += 4) {
+      char* lds = st + base + kk * 1024;
+      const int off = 16 * ln + base + kk * 1024;
+      load_lds16<0>(rk, lds, off);
+      if constexpr (C::LOADS_PER_WAVE > 1) load_lds16<1024>(rk, lds, off);
+      if constexpr (C::LOADS_PER_WAVE > 2) load_lds16<2048>(rk, lds, off);
+      if constexpr (C::LOADS_PER_WAVE > 3) load_lds16<3072>(rk, lds, off);
     }
-    // The column tables (inverse norms, then positions) in 256-byte pieces, 4 bytes a lane.
-    const int tbytes = (left < C::TN ? left : C::TN) * 4;
-#pragma unroll
-    for (int pc4 = wave; pc4 < C::TN / 32; pc4 += NWAVES) {
-      const int part = pc4 % (C::TN / 64);
-      const int rem = tbytes - part * 256;
-      const void* src = pc4 < C::TN / 64 ? (const void*)(rc + first + part * 64)
-                                          : (const void*)(pc + first + part * 64);
-      load_block_lds4(src, rem > 0 ? rem : 0, 4 * lane, st + C::KEY_BYTES + pc4 * 256);
-    }
+    // The r' table in 256-byte pieces, 4 bytes a lane.
+    if (wave < C::TN / 64)
+      load_lds4(tile_rsrc(rc + first, ncol * 4), st + C::KEY_BYTES + wave * 256,
+                4 * ln + wave * 256);
   };
-  auto finish_tile = [&]() {  // wait for this wave's direct loads of the issued tile
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  auto finish_tile = [&]() {  // wait for this wave's direct loads and its LDS maxima
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   };
 
-  // ---- the pending reduction: the last 32-row block of the previous chunk is reduced
-  // while the first MFMA chain of the next chunk runs (software pipelining across chunks).
-  f32x16 pacc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float prv[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) prv[v] = 0.0f;
-  int pgc = 0;
-  uint32_t pmask = 0u;  // result mask of the pending chunk (zero: dropped)
-
-  // Chunk gc (chunk kc of its tile) into row block s.  With FG = CPT the chunks of a tile
-  // are merged in tb first and the tile enters the running best at ``flush``.
-  auto reduce_into = [&](const f32x16& acc, const float (&rv)[16], int gc, int kc, int s,
-                         uint32_t m) {
+  // ---- reductions of one 32 x 32 block (rows of block s, one chunk's columns) ------------
+  // Row direction with the chunk's code; column direction into cb (one best per row block).
+  struct ColBest {
+    uint32_t b[NSUB];
+  };
+  auto reduce_block = [&](const f32x16& acc, int s, bool odd, float rl, uint32_t m,
+                          uint32_t code, ColBest& cb) {
+    // a dropped block (m = 0): r' and the bias become 0, below any candidate
+    const float bias = __uint_as_float(m & kBias);
+    rl = __uint_as_float(__float_as_uint(rl) & m);
     if constexpr (COUNT) {
-      run[s] += chunk_count(acc, rv, thr[s]) & m;
-    } else if constexpr (FG == 1) {
-      const uint32_t best = chunk_best<1>(acc, rv, 0) & m;
-      run_update<1>(best, gc, run[s], cid[s]);
+      uint32_t neg = 0u;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint32_t y = __float_as_uint(fmaf(acc[v], rl, rs[s][v]));
+        run[s][v] = __builtin_amdgcn_alignbit(run[s][v], y, 31);
+        neg = __builtin_amdgcn_alignbit(neg, y, 31);
+      }
+      cb.b[s] = (16u - (uint32_t)__builtin_popcount(neg)) & m;
     } else {
-      tb[s] = max(tb[s], chunk_best<FG>(acc, rv, kc) & m);
+      uint32_t b = 0u;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint32_t us = (__float_as_uint(fmaf(acc[v], rl, bias)) & ~LOW) | code;
+        if (s == NSUB - 1 && v >= C::HOLD_LAST) {
+          run[s][v] = max(run[s][v], us);
+          asm("" : "+v"(run[s][v]));  // (kept from merging with the next chunk's candidates)
+        } else if (odd) {
+          run[s][v] = max(max(run[s][v], hold[s][v]), us);
+        } else {
+          hold[s][v] = us;
+        }
+        b = max(b, (__float_as_uint(fmaf(acc[v], rs[s][v], 3.0f)) & ~LOW) | (uint32_t)(15 - v));
+      }
+      cb.b[s] = b & m;
     }
   };
-  auto flush = [&](int s, int c0) {
-    if constexpr (!COUNT && FG > 1) {
-      run_update<FG>(tb[s], c0, run[s], cid[s]);
-      tb[s] = 0u;
+  // The column candidate of a chunk over the wave's row blocks: value bits and ~slot (zero value:
+  // none); equal values keep the earlier row block, and inside it the earlier register.
+  const uint32_t nrow = ~(uint32_t)(row0 + 4 * half);
+  auto col_key = [&](const ColBest& cb) -> u64 {
+    uint32_t b = cb.b[0], off = 0u;
+#pragma unroll
+    for (int s = 1; s < NSUB; ++s) {
+      const bool up = (cb.b[s] >> BITS) > (b >> BITS);
+      b = up ? cb.b[s] : b;
+      off = up ? 32u * s : off;
+    }
+    const uint32_t q = 15u - (b & 15u);
+    return ((u64)(b & ~LOW) << 32) | (nrow - off - q - (q & ~3u));
+  };
+  // A chunk's column result (count mode: the count), and its merge into the tile's entries.
+  auto col_result = [&](const ColBest& cb) -> u64 {
+    if constexpr (COUNT) {
+      uint32_t c = 0u;
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) c += cb.b[s];
+      return c;
+    } else {
+      return col_key(cb);
+    }
+  };
+  const uint32_t col_lane = lds_offset(s_col) + 8 * (l32 + (COUNT ? 0 : grp * C::TN));
+  auto col_emit = [&](u64 r, int buf3, int kc) {
+    const uint32_t off = col_lane + 8 * (buf3 * 2 * C::TN + kc * kChunk);
+    if constexpr (COUNT) add_lds(off, (uint32_t)r);
+    else max_lds(off, r);
+  };
+  // A complete tile's column results to global memory; the LDS entries start over.
+  auto cols_out = [&](int tile, int buf3) {
+    constexpr int WPG = C::TN / 64;  // waves per group's entries
+    const int g = wave / WPG;
+    if (g < 2) {
+      int ln = lane;
+      asm("" : "+v"(ln));
+      const int c0 = (wave % WPG) * 64;
+      u64* p = s_col + (buf3 * 2 + g) * C::TN + c0 + ln;
+      const u64 v = *p;
+      *p = 0ull;
+      const int col0 = tile * C::TN + c0;
+      if constexpr (COUNT) {
+        if ((uint32_t)v != 0u && col0 + ln < pl.len) atomicAdd(&counts[col0 + ln], (int)(uint32_t)v);
+      } else {
+        u64* dst = best0 + (g ? plane : 0) + col0;
+        if ((uint32_t)(v >> 32) >= kValidMin && col0 + ln < ncols) max_global(dst + ln, v);
+      }
+    }
+  };
+  // End of a window of the row direction: chunk base + i * stride is coded LOW - i; dst is the
+  // candidates' plane (by the group of the columns).
+  auto rows_out = [&](int base, int stride, u64* dst) {
+    if constexpr (!COUNT) {
+      u64 key[NSUB];
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) {
+        key[s] = reduce_rows_max(run[s], l32);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) run[s][v] = 0u;
+      }
+      // even lanes write the rows of block s0, odd lanes those of block s0 + 1 (if there is one)
+#pragma unroll
+      for (int s0 = 0; s0 < NSUB; s0 += 2) {
+        constexpr int kOne = NSUB > 1 ? 1 : 0;
+        const bool second = s0 + 1 < NSUB && (lane & 1);
+        const u64 ka = key[s0], kb2 = key[s0 + 1 < NSUB ? s0 + kOne : s0];
+        const u64 kx = second ? kb2 : ka;
+        const uint32_t val = (uint32_t)(kx >> 32);
+        const int chunk = base + (int)(LOW - (val & LOW)) * stride;
+        const uint32_t slot = (uint32_t)(chunk * kChunk + 31 - (int)(kx & 31u));
+        const int row = row0 + 32 * (s0 + second) + slot_row(reduced_reg(l32), half);
+        if (val >= kValidMin && row < nslots && (s0 + 1 < NSUB || !(lane & 1)))
+          max_global(dst + row, ((u64)(val & ~LOW) << 32) | (uint32_t)~slot);
+      }
+    }
+  };
+  auto counts_fold = [&]() {  // count mode: a window's sign bits into the counts
+    if constexpr (COUNT) {
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          cnt[s][v / 4] += (uint32_t)__builtin_popcount(~run[s][v] & kept[s]) << (8 * (v & 3));
+          run[s][v] = 0u;
+        }
+        kept[s] = 0u;
+      }
+    }
+  };
+  auto counts_out = [&]() {  // count mode: the rows' counts so far
+    if constexpr (COUNT) {
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) {
+        uint32_t cs[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) cs[v] = (cnt[s][v / 4] >> (8 * (v & 3))) & 0xFFu;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) cnt[s][v] = 0u;
+        const uint32_t c = reduce_rows_sum(cs, l32);
+        const int row = row0 + 32 * s + slot_row(reduced_reg(l32), half);
+        if (c != 0u && row < pl.len && !(lane & 1))
+          atomicAdd(&counts[row], (int)c);
+      }
     }
   };
 
-  // One tile: each chain's epilogue runs beside the following chain's MFMAs, and the last
-  // chain's epilogue is left pending for the next chunk.  During the last chain, k-step t of
-  // the next chunk's A fragments is read into the registers that MFMA t has just consumed.
-  auto sweep_tile = [&](auto buf_tag, int c0, uint32_t keep) {
-    constexpr int BUF = decltype(buf_tag)::value;
-    const char* st = smem + BUF * C::STAGE;
-    bf16x8 fc[C::KSTEPS];
+  // ---- the pending reduction: the last row block of the previous chunk is reduced while the
+  // first MFMA chain of the next chunk runs (software pipelining across chunks).
+  f32x16 pacc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float prl = 0.0f;
+  uint32_t pcode = 0u, pm_mask = 0u;
+  ColBest pcb;
 #pragma unroll
-    for (int t = 0; t < C::KSTEPS; ++t)
-      fc[t] = *reinterpret_cast<const bf16x8*>(st + aoff[t]);
+  for (int s = 0; s < NSUB; ++s) pcb.b[s] = 0u;
+
+  // One tile: each chain's reductions run beside the following chain's MFMAs, and the last
+  // chain's are left pending for the next chunk.  During the last chain, fragment t of the next
+  // chunk is read into the registers that MFMA t has just consumed.
+  auto sweep_tile = [&](uint32_t stage, int c0, uint32_t keep, int wbase,
+                        int buf3, int pbuf3) {
+    // VALU instructions placed beside each MFMA: one block's reductions over its MFMAs
+    constexpr int VALU_PER_MFMA =
+        ((COUNT ? 54 : 86) + (SPLIT ? 32 : 0) + C::MFMAS - 1) / C::MFMAS;
+    const uint32_t fbase = lane_base + stage;
+    const char* st = smem + stage;
+    bf16x8 fb[C::UF];
+    u64 cres = 0ull;  // the pending chunk's column result
+#pragma unroll
+    for (int t = 0; t < C::UF; ++t) fb[t] = read_frag(fbase, t, 0);
 #pragma unroll
     for (int kc = 0; kc < CPT; ++kc) {
-      const int gc = c0 + kc;
-      const uint32_t m = 0u - ((keep >> kc) & 1u);
-      // with bands per row block, the result mask of row block sb for this chunk
-      auto mask_of = [&](int sb) -> uint32_t {
-        if constexpr (SUB_BANDS) return 0u - ((keep >> (kc * NSUB + sb)) & 1u);
-        else return m;
-      };
-      float rcur[16];
-      // with a single row block, chain 0 is also the last chain and carries the prefetch
-      const bool pre0 = (NSUB == 1) && (kc + 1 < CPT);
-      f32x16 x = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      auto mask_of = [&](int) -> uint32_t { return 0u - ((keep >> kc) & 1u); };
+      const float rl = *reinterpret_cast<const float*>(st + C::KEY_BYTES + (kc * kChunk + l32) * 4);
+      // (in a vector register: the value mask takes the one scalar operand of v_and_or)
+      uint32_t code = LOW - (uint32_t)(c0 + kc - wbase);
+      asm("" : "+v"(code));
+      ColBest cb;
+      f32x16 x;
 #pragma unroll
-      for (int t = 0; t < C::KSTEPS; ++t) {
-        x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[t], bfrag[0][t], x, 0, 0, 0);
-        if (pre0)
-          fc[t] = *reinterpret_cast<const bf16x8*>(st + (kc + 1) * C::CHUNK_BYTES + aoff[t]);
-      }
-      // the pending chunk: the previous chunk of this tile, or the last of the previous tile
-      reduce_into(pacc, prv, pgc, kc == 0 ? CPT - 1 : kc - 1, NSUB - 1, pmask);
-      if (kc == 0) flush(NSUB - 1, c0 - CPT);
-      load_rv(st, kc, rcur);
-#pragma unroll
-      for (int i = 0; i < C::KSTEPS; ++i) {
-        __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
-        if (i < 4 || pre0) __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(kSchedValu, C::VALU_PER_MFMA, 0);
-      }
-#pragma unroll
-      for (int s = 1; s < NSUB; ++s) {
+      for (int s = 0; s < NSUB; ++s) {
         f32x16 y = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        f32x16 yp = y, yq = y;
         const bool pre = (s == NSUB - 1) && (kc + 1 < CPT);
 #pragma unroll
-        for (int t = 0; t < C::KSTEPS; ++t) {
-          y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[t], bfrag[s][t], y, 0, 0, 0);
-          if (pre)
-            fc[t] = *reinterpret_cast<const bf16x8*>(st + (kc + 1) * C::CHUNK_BYTES + aoff[t]);
+        for (int t = 0; t < C::UF; ++t) {
+          if constexpr (!SPLIT) {
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
+          } else if (t < G) {
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
+            yp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][G + t], fb[t], yp, 0, 0, 0);
+          } else {
+            yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t - G], fb[t], yq, 0, 0, 0);
+          }
+          if (pre) fb[t] = read_frag(fbase, t, kc + 1);
         }
-        reduce_into(x, rcur, gc, kc, s - 1, mask_of(s - 1));
-        if (kc == CPT - 1) flush(s - 1, c0);
+        if (s == 0) {
+          // the pending chunk: the previous chunk of this tile, or the last of the previous tile
+          kept[NSUB - 1] = (kept[NSUB - 1] << 1) | (pm_mask & 1u);
+          reduce_block(pacc, NSUB - 1, kc == 0 ? true : ((kc - 1) & 1) != 0, prl, pm_mask, pcode, pcb);
+          cres = col_result(pcb);
+        } else {
+          kept[s - 1] = (kept[s - 1] << 1) | (mask_of(s - 1) & 1u);
+          reduce_block(x, s - 1, (kc & 1) != 0, rl, mask_of(s - 1), code, cb);
+        }
 #pragma unroll
-        for (int i = 0; i < C::KSTEPS; ++i) {
+        for (int i = 0; i < C::MFMAS; ++i) {
           __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
           if (pre) __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(kSchedValu, C::VALU_PER_MFMA, 0);
+          __builtin_amdgcn_sched_group_barrier(kSchedValu, VALU_PER_MFMA, 0);
         }
-        x = y;
+        __builtin_amdgcn_sched_barrier(0);
+        if (s == 0) {
+          col_emit(cres, kc == 0 ? pbuf3 : buf3, kc == 0 ? CPT - 1 : kc - 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (SPLIT) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) x[v] = y[v] + (yp[v] + yq[v]);
+        } else {
+          x = y;
+        }
       }
       pacc = x;
+      prl = rl;
+      pcode = code;
+      pm_mask = mask_of(NSUB - 1);
+      pcb = cb;
+    }
+  };
+  // Reduce the pending block now, with nothing left pending.
+  auto drain = [&](int pbuf3) {
+    // The opaque copy keeps the compiler from moving the tile body's own pending reduction out of
+    // the body to share it with this rare path.
+    f32x16 pa = pacc;
+    asm volatile("" : "+v"(pa));
+    kept[NSUB - 1] = (kept[NSUB - 1] << 1) | (pm_mask & 1u);
+    reduce_block(pa, NSUB - 1, true, prl, pm_mask, pcode, pcb);
+    col_emit(col_result(pcb), pbuf3, CPT - 1);
+    prl = 0.0f;
+    pm_mask = 0u;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) prv[v] = rcur[v];
-      pgc = gc;
-      pmask = mask_of(NSUB - 1);
+    for (int s = 0; s < NSUB; ++s) pcb.b[s] = 0u;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      pacc[v] = 0.0f;
+      hold[NSUB - 1][v] = 0u;
     }
   };
 
-  // A wave whose rows all lie past the end of the sequence (in the last row block of a
-  // sequence) only takes its share of the tile loads; its SIMD's MFMA pipe is left to the
-  // other workgroup's wave.
-  const bool active = wrow0 < len;
 #ifdef TWINKV_DEBUG
-  // Debug build: both stages and the parked results start as poison.
+  // Debug build: both stages start as poison.
   {
     uint4* all = reinterpret_cast<uint4*>(smem);
-    for (int i = threadIdx.x; i < (2 * C::STAGE + C::RETIRED) / 16; i += C::NT)
+    for (int i = threadIdx.x; i < 2 * C::STAGE / 16; i += C::NT)
       all[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
   }
   __syncthreads();
 #endif
-  if (ntiles > 0) issue_tile(0, 0);
+  for (int e = threadIdx.x; e < 3 * 2 * C::TN; e += C::NT) s_col[e] = 0ull;
+  for (int e = threadIdx.x; e < C::RB; e += C::NT) {
+    const int slot = pl.rb * C::RB + e, g = slot >= ret_pad ? 1 : 0;
+    s_pos[e] = g == 0 && pl.n_ret == 0 ? 0 : slot_position(a, pl, slot, g);
+  }
+  // Tiles from the last down to the rows' own: the row blocks of a problem that run at the same
+  // time start on the same tile and stay near each other, so a tile is read from HBM about once
+  // (sweeping up from each block's own rows spreads them over the whole problem).
+  if (ta < tb) issue_tile(tb - 1, 0);
+  bool open = false;     // a window of the row direction is open
+  bool pending = false;  // ... and its last block is pending
+  int wbase = 0;         // ... its first chunk
+  int nacc = 0;          // (count mode) chunks counted since the counts were written out
+  int buf3 = 0;          // candidates' buffer of this tile: iteration % 3
 #pragma unroll 1
-  for (int tile = 0; tile < ntiles; ++tile) {
-    const int buf = tile & 1;
+  for (int tile = tb - 1; tile >= ta; --tile) {
+    const int buf = (tb - 1 - tile) & 1;
+    const int pbuf3 = buf3 == 0 ? 2 : buf3 - 1;
     finish_tile();
     __syncthreads();
-    if (tile + 1 < ntiles) issue_tile(tile + 1, buf ^ 1);
+    if (tile > ta) issue_tile(tile - 1, buf ^ 1);
+    // every wave has finished the tile before the previous one (its last block is reduced in the
+    // tile after it)
+    if (tile + 2 < tb) cols_out(tile + 2, buf3 == 2 ? 0 : buf3 + 1);
     const int c0 = tile * CPT;
-    if (c0 == ret_chunks) {
-      // First evicted chunk: finish the pending S0 reduction here and park the S0 results.
-      // The opaque copy keeps the compiler from moving the tile body's own pending
-      // reduction out of the body to share it with this rare path.
-      f32x16 pa = pacc;
-      asm volatile("" : "+v"(pa));
-      reduce_into(pa, prv, pgc, CPT - 1, NSUB - 1, pmask);
-      flush(NSUB - 1, c0 - CPT);
-      pmask = 0u;
-      retire();
+    const uint32_t keep = active ? __builtin_amdgcn_readfirstlane(keep_bits(c0)) : 0u;
+    const bool work = keep != 0u;  // (tiles of dropped chunks only are skipped)
+    // the window ends after its last chunk, at the end of a group of columns and with the sweep
+    const bool close = open && (c0 < wbase || (!COUNT && c0 + CPT == ret_chunks));
+    if (pending && (close || !work)) {
+      drain(pbuf3);
+      pending = false;
+      if constexpr (COUNT) counts_fold();
     }
-    const uint32_t keep = __builtin_amdgcn_readfirstlane(keep_bits(c0));
-    if (active) {
-      if (buf == 0) sweep_tile(std::integral_constant<int, 0>{}, c0, keep);
-      else sweep_tile(std::integral_constant<int, 1>{}, c0, keep);
+    if (close) {
+      if constexpr (COUNT) {
+        nacc += 32;
+        if (nacc > 190) {  // a lane's counts still fit 8 bits
+          counts_out();
+          nacc = 0;
+        }
+      } else {
+        rows_out(wbase, 1, best0 + (!COUNT && c0 + CPT >= ret_chunks ? plane : 0));
+      }
+      open = false;
     }
+    if (work) {
+      if (!open) wbase = c0 + CPT - (COUNT ? 32 : C::WIN);
+      open = true;
+      sweep_tile((uint32_t)(buf * C::STAGE), c0, keep, wbase, buf3, pbuf3);
+      pending = true;
+    }
+    buf3 = buf3 == 2 ? 0 : buf3 + 1;
 #ifdef TWINKV_DEBUG
     // Debug build: once every wave has swept this stage, fill it with 0xFF bytes (NaN keys
-    // and inverse norms, position -1) before the next tile's loads refill it.  A read of a
-    // stage outside its tile's lifetime then sees the poison, and the results differ from
-    // the normal build's.
+    // and inverse norms) before the next tile's loads refill it.  A read of a stage outside its
+    // tile's lifetime then sees the poison, and the results differ from the normal build's.
     __syncthreads();
     {
       uint4* stg = reinterpret_cast<uint4*>(smem + buf * C::STAGE);
@@ -657,255 +736,211 @@ void sim_reduce_kernel(SimArgs a) {
     __syncthreads();
 #endif
   }
-  reduce_into(pacc, prv, pgc, CPT - 1, NSUB - 1, pmask);
-  flush(NSUB - 1, (ntiles - 1) * CPT);
-  if (!retired_done) retire();          // no evicted columns were swept
+  if (pending) {
+    drain(buf3 == 0 ? 2 : buf3 - 1);
+    if constexpr (COUNT) counts_fold();
+  }
   if constexpr (!COUNT) {
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) to_chunk_form<FG>(run[s], cid[s]);
+    if (open) rows_out(wbase, 1, best0 + (!COUNT && ta * CPT >= ret_chunks ? plane : 0));
   }
+  finish_tile();
+  __syncthreads();
+  if (tb - ta >= 2) cols_out(ta + 1, buf3 == 2 ? 0 : buf3 + 1);
+  if (tb - ta >= 1) cols_out(ta, buf3 == 0 ? 2 : buf3 - 1);
 
-  // ---- masked pass: the chunks holding window pairs or padding next to real columns, read
-  // straight from the column copy, with the window / padding test per element.  Chunks are
-  // visited out of order here, so equal values keep the smaller chunk index explicitly.
-  //
-  // Maximum with the tile merge: in each group the columns whose positions lie within w of a
-  // lane's row form one contiguous range of column indices, read off the S0 prefix counts,
-  // so the test per element is one unsigned range compare and the position list is not read.
-  // The copies of a group's last column in its partly filled last chunk are excluded with
-  // that column (and otherwise only tie with it).
-  constexpr bool RANGE_TEST = !COUNT && FG > 1;
-  // S0 prefix counts at the two ends of each row's window (loaded here, used once the first
-  // chunks' loads are in flight)
-  int wrx[NSUB], wry[NSUB];
-  if constexpr (RANGE_TEST) {
-    const int32_t* prk = a.prank + colbase;
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) {
-      const int i = min(wrow0 + s * 32 + l32, len - 1);
-      wrx[s] = prk[max(i - a.w, 0)];
-      wry[s] = prk[min(i + a.w + 1, len)];
-    }
-  }
-  // First excluded column and number of excluded columns of row block s's lane row in group
-  // grp.
-  auto excluded_range = [&](int grp, int s, int& lo, int& num) {
-    // opaque copies: computed here, in each chunk's step, not hoisted ahead of the chunk loads
-    int rx = wrx[s], ry = wry[s];
-    asm volatile("" : "+v"(rx), "+v"(ry));
-    const int i = min(wrow0 + s * 32 + l32, len - 1);
-    const int x = max(i - a.w, 0), y = min(i + a.w + 1, len);
-    const int ret_pad = ret_chunks * kChunk;
-    if (grp == 0) {
-      lo = rx;
-      num = (ry == pm.n_ret ? ret_pad : ry) - lo;
-    } else {
-      lo = ret_pad + x - rx;
-      const int e = ret_pad + y - ry;
-      num = (e == ret_pad + (len - pm.n_ret) ? pm.total_chunks * kChunk : e) - lo;
-    }
-  };
-  struct MaskedChunk {  // one chunk's A fragments and column tables, in registers (two
-                        // chunks per memory round trip measured slower)
-    bf16x8 af[C::KSTEPS];
-    float rv[16];
-    int jv[16];
-  };
-  auto masked_load = [&](int gc, MaskedChunk& mc) {
-    const int col = gc * kChunk + l32;
-#pragma unroll
-    for (int t = 0; t < C::KSTEPS; ++t)
-      mc.af[t] = *reinterpret_cast<const bf16x8*>(pk + (int64_t)col * C::DCOL +
-                                                  col_off<D, SPLIT>(t) + 8 * half);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int cc = gc * kChunk + slot_col(v, half);
-      mc.rv[v] = rc[cc];
-      mc.jv[v] = RANGE_TEST ? 0 : pc[cc];
-    }
-  };
-  auto masked_compute = [&](int gc, int grp, const MaskedChunk& mc, uint32_t (&rs)[NSUB],
-                            int (&cs)[NSUB]) {
-    const bf16x8 (&af)[C::KSTEPS] = mc.af;
-    const float (&rv)[16] = mc.rv;
-    const int (&jv)[16] = mc.jv;
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) {
-      if constexpr (SUB_BANDS) {
-        // only the row blocks that dropped this chunk in the sweep
-        const bool need = grp == 0 ? (gc == pad_r || (gc >= sr_lo[s] && gc <= sr_hi[s]))
-                                   : (gc == pad_e || (gc >= se_lo[s] && gc <= se_hi[s]));
-        if (!need) continue;
-      }
-      f32x16 x = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < C::KSTEPS; ++t)
-        x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[t], bfrag[s][t], x, 0, 0, 0);
-      const int i = wrow0 + s * 32 + l32;
-      if constexpr (COUNT) {
-        uint32_t c = 0u;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const uint32_t ok = (uint32_t)(jv[v] >= 0) & (uint32_t)(abs(i - jv[v]) > a.w);
-          c += ok & ((~__float_as_uint(fmaf(x[v], rv[v], thr[s]))) >> 31);
-        }
-        rs[s] += c;
-      } else {
-        uint32_t best = 0u;
-        // column of slot v, relative to the first excluded column of this row's range
-        int xlo = 0, xnum = 0;
-        if constexpr (RANGE_TEST) excluded_range(grp, s, xlo, xnum);
-        const uint32_t rel = (uint32_t)(gc * kChunk + 4 * half - xlo);
-        const uint32_t nex = (uint32_t)xnum;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float y = fmaf(x[v], rv[v], 3.0f);
-          const uint32_t u = (__float_as_uint(y) & ~LOW) | (uint32_t)(15 - v);
-          bool ok;
-          if constexpr (RANGE_TEST) ok = rel + (uint32_t)(8 * (v >> 2) + (v & 3)) >= nex;
-          else ok = (jv[v] >= 0) & (abs(i - jv[v]) > a.w);
-          best = max(best, ok ? u : 0u);
-        }
-        const bool upd = (best >> 4) > (rs[s] >> 4) ||
-                         ((best >> 4) == (rs[s] >> 4) && best >= kValidMin && gc < cs[s]);
-        rs[s] = upd ? best : rs[s];
-        cs[s] = upd ? gc : cs[s];
-      }
-    }
-  };
-  auto masked_range = [&](int l, int h, int grp, uint32_t (&rs)[NSUB], int (&cs)[NSUB]) {
+  // ---- the dropped chunks that hold real pairs, read straight from the column copy, every element
+  // tested (the other workgroup of the CU sweeps meanwhile).  Segment k takes every nseg-th.
+  if (!active) return;
+  auto masked_range = [&](int l, int h, int cgrp) {
+    u64* const dst_rows = best0 + (cgrp ? plane : 0);
+    u64* const dst_cols = best0 + (grp ? plane : 0);
+    int n = 0;
 #pragma unroll 1
-    for (int gc = l; gc <= h; ++gc) {
-      if (gc < nchunks) {
-        MaskedChunk mc;
-        masked_load(gc, mc);
-        masked_compute(gc, grp, mc, rs, cs);
+    for (int gc = l + seg; gc <= h; gc += nseg) {
+      const int col = gc * kChunk + l32;
+      bf16x8 fb[C::UF];
+      const uint16_t* src = pk + (int64_t)gc * (kChunk * C::DCOL) + 8 * lane;
+#pragma unroll
+      for (int t = 0; t < C::UF; ++t) fb[t] = *reinterpret_cast<const bf16x8*>(src + 512 * t);
+      const float rl = rc[col];
+      // (counting, columns of padding are excluded: position -1)
+      const int pj = COUNT ? a.pcol[pl.colbase + col] : slot_position(a, pl, col, cgrp);
+      const Window win = window_of(pj, a.w, cgrp == grp);
+      const uint32_t code = LOW - (uint32_t)n;
+      ColBest cb;
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) {
+        cb.b[s] = 0u;
+        if (cgrp == grp && gc < row0 / kChunk + s) continue;  // the other half of the triangle
+        f32x16 y = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        f32x16 yp = y, yq = y;
+#pragma unroll
+        for (int t = 0; t < C::UF; ++t) {
+          if constexpr (!SPLIT) {
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
+          } else if (t < G) {
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
+            yp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][G + t], fb[t], yp, 0, 0, 0);
+          } else {
+            yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t - G], fb[t], yq, 0, 0, 0);
+          }
+        }
+        if constexpr (SPLIT) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) y[v] = y[v] + (yp[v] + yq[v]);
+        }
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+          const int4 p4 = *reinterpret_cast<const int4*>(s_pos + wave * C::WR + 32 * s + 8 * v4 + 4 * half);
+          const int pi[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int v = 4 * v4 + e;
+            const bool ok = win.base - (uint32_t)pi[e] >= win.thr;
+            if constexpr (COUNT) {
+              const uint32_t c = (uint32_t)ok & ((~__float_as_uint(fmaf(y[v], rl, rs[s][v]))) >> 31);
+              cnt[s][v / 4] += c << (8 * (v & 3));
+              cb.b[s] += c;
+            } else {
+              const uint32_t us = (__float_as_uint(fmaf(y[v], rl, 3.0f)) & ~LOW) | code;
+              const uint32_t ut = (__float_as_uint(fmaf(y[v], rs[s][v], 3.0f)) & ~LOW) | (uint32_t)(15 - v);
+              run[s][v] = max(run[s][v], ok ? us : 0u);
+              cb.b[s] = max(cb.b[s], ok ? ut : 0u);
+            }
+          }
+        }
+      }
+      if constexpr (COUNT) {
+        const uint32_t c = (uint32_t)col_result(cb);
+        if (c != 0u) atomicAdd(&counts[col], (int)c);
+        if (++n == 32) {  // a lane's counts still fit 8 bits (at most 224 from the sweep)
+          counts_out();
+          n = -192;
+        }
+      } else {
+        const u64 key = col_key(cb);  // the better of the two halves' rows
+        const auto sh = __builtin_amdgcn_permlane32_swap((uint32_t)(key >> 32), (uint32_t)(key >> 32), false, false);
+        const auto sl = __builtin_amdgcn_permlane32_swap((uint32_t)key, (uint32_t)key, false, false);
+        const u64 k0 = ((u64)sh[0] << 32) | sl[0], k1 = ((u64)sh[1] << 32) | sl[1];
+        const u64 kx = k0 > k1 ? k0 : k1;
+        if (half == 0 && (uint32_t)(kx >> 32) >= kValidMin) max_global(dst_cols + col, kx);
+        ++n;
+        if (n == C::WIN || gc + nseg > h) {
+          rows_out(gc - (n - 1) * nseg, nseg, dst_rows);
+          n = 0;
+        }
       }
     }
   };
-  // evicted group: the live registers
-  if (active && a.want_all) {
-    masked_range(ce_lo, ce_hi, 1, run, cid);
-    if (pad_e >= 0 && !(pad_e >= ce_lo && pad_e <= ce_hi)) masked_range(pad_e, pad_e, 1, run, cid);
+  if constexpr (COUNT) counts_out();
+#pragma unroll 1
+  for (int r = 0; r < 3; ++r) {  // (one copy of the code)
+    const int l = r == 0 ? row0 / kChunk : (r == 1 ? bd.b_lo : pad_c);
+    const int h = r == 0 ? bd.a_hi : (r == 1 ? bd.b_hi : (pad_c > bd.a_hi ? pad_c : -1));
+    masked_range(l, h, r == 1 ? grp ^ 1 : grp);
   }
-  // S0 group: the parked results
-  {
-    uint32_t rr[NSUB];
-    int rcid[NSUB];
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) {
-      const uint2 v = retired[s * 64 + lane];
-      rr[s] = v.x;
-      rcid[s] = (int)v.y;
-    }
-    if (active) {
-      masked_range(cr_lo, cr_hi, 0, rr, rcid);
-      if (pad_r >= 0 && !(pad_r >= cr_lo && pad_r <= cr_hi)) masked_range(pad_r, pad_r, 0, rr, rcid);
-    }
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) retired[s * 64 + lane] = make_uint2(rr[s], (uint32_t)rcid[s]);
-  }
-
-  // ---- resolve: lanes l and l+32 hold the same row over disjoint column halves ----------
-  if constexpr (COUNT) {
-    // the S0 group is empty in count mode: every column was swept as an evicted column
-#pragma unroll
-    for (int s = 0; s < NSUB; ++s) {
-      const int i = wrow0 + s * 32 + l32;
-      const uint32_t total = run[s] + __shfl_xor(run[s], 32);
-      if (half == 0 && i < len) a.counts[(int64_t)head * a.T + si.start + i] = (int32_t)total;
-    }
-    return;
-  }
-#pragma unroll
-  for (int s = 0; s < NSUB; ++s) {
-    const int i = wrow0 + s * 32 + l32;
-    const float ri = (i < len) ? rinv[i] : 0.0f;
-    const float g = row_scale(ri);
-    uint32_t val[2];
-    int pos[2];
-    const uint2 rr = retired[s * 64 + lane];
-    const uint32_t runs[2] = {rr.x, run[s]};
-    const int cids[2] = {(int)rr.y, cid[s]};
-#pragma unroll
-    for (int grp = 0; grp < 2; ++grp) {
-      uint32_t v = runs[grp] & ~LOW;
-      int p = cids[grp] * kChunk + slot_col(15 - (int)(runs[grp] & 15u), half);
-      // a slot past the group's last column holds a copy of that column
-      if constexpr (FG > 1)
-        p = min(p, grp == 0 ? pm.n_ret - 1 : ret_chunks * kChunk + (len - pm.n_ret) - 1);
-      const uint32_t v2 = __shfl_xor(v, 32);
-      const int p2 = __shfl_xor(p, 32);
-      if (v2 > v || (v2 == v && p2 < p)) { v = v2; p = p2; }
-      val[grp] = v;
-      pos[grp] = p;
-    }
-    if (half == 0 && i < len) {
-      const int64_t o = (int64_t)head * a.T + si.start + i;
-      const bool vr = val[0] >= kValidMin;
-      const bool ve = val[1] >= kValidMin;
-      const int jr = vr ? pc[pos[0]] : -1;
-      const int je = ve ? pc[pos[1]] : -1;
-      const float sr = vr ? (__uint_as_float(val[0]) - 3.0f) * ri / g : -1.0f;
-      const float se = ve ? (__uint_as_float(val[1]) - 3.0f) * ri / g : -1.0f;
-      if (a.best_ret) a.best_ret[o] = sr;
-      if (a.arg_ret) a.arg_ret[o] = jr;
-      if (a.best_all || a.arg_all) {
-        bool take_r;
-        if (!vr) take_r = false;
-        else if (!ve) take_r = true;
-        else take_r = (val[0] > val[1]) || (val[0] == val[1] && jr < je);
-        const bool any = vr || ve;
-        if (a.best_all) a.best_all[o] = any ? (take_r ? sr : se) : -1.0f;
-        if (a.arg_all) a.arg_all[o] = any ? (take_r ? jr : je) : -1;
-      }
-    }
-  }
+  if constexpr (COUNT) counts_out();
 }
 
-template <int D, bool SPLIT, int NSUB, int NWAVES, int CPT, int OCC, int FG>
+constexpr int kFlatThreads = 256;
+
+// Zero 16-byte pieces (the counts before a sweep; the tail of the last piece is cleared word by
+// word).
+__global__ __launch_bounds__(kFlatThreads) void clear_kernel(uint32_t* __restrict__ p, int64_t words) {
+  const int64_t i = ((int64_t)blockIdx.x * kFlatThreads + threadIdx.x) * 4;
+  for (int e = 0; e < 4; ++e)
+    if (i + e < words) p[i + e] = 0u;
+}
+
+// The candidates of every token to its results: best_ret / arg_ret from plane 0 (S0 columns),
+// best_all / arg_all from both planes.
+__global__ __launch_bounds__(kFlatThreads) void finish_kernel(SimArgs a, int h0) {
+  const int64_t t = (int64_t)blockIdx.x * kFlatThreads + threadIdx.x;
+  if (t >= a.T) return;
+  const int head = h0 + (int)blockIdx.y;
+  int lo = 0, hi = a.n_seqs - 1;  // the last sequence that starts at or before t
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (a.seqtab[mid].start <= t) lo = mid; else hi = mid - 1;
+  }
+  const SeqInfo si = a.seqtab[lo];
+  const ProblemMeta pm = a.pmeta[head * a.n_seqs + lo];
+  const int64_t colbase = (int64_t)head * a.PT + si.perm_off;
+  const int i = (int)(t - si.start);
+  const int r0 = a.prank[colbase + i], r1 = a.prank[colbase + i + 1];
+  const int slot = r1 > r0 ? r0 : pm.ret_chunks * kChunk + (i - r0);
+  const int64_t o = (int64_t)head * a.T + t;
+  const float ri = a.rinv[o];
+  const u64* best = reinterpret_cast<const u64*>(a.best) + colbase;
+  const int32_t* pc = a.pcol + colbase;
+  const u64 kr = best[slot];
+  const uint32_t vr = (uint32_t)(kr >> 32);
+  const int jr = vr >= kValidMin ? pc[~(uint32_t)kr] : -1;
+  if (a.best_ret) a.best_ret[o] = jr >= 0 ? similarity(vr, ri) : -1.0f;
+  if (a.arg_ret) a.arg_ret[o] = jr;
+  const u64 ke = best[(int64_t)a.n_heads * a.PT + slot];
+  const uint32_t ve = (uint32_t)(ke >> 32);
+  const int je = ve >= kValidMin ? pc[~(uint32_t)ke] : -1;
+  const bool take_r = jr >= 0 && (je < 0 || vr > ve || (vr == ve && jr < je));
+  const int j = take_r ? jr : je;
+  if (a.best_all) a.best_all[o] = j >= 0 ? similarity(take_r ? vr : ve, ri) : -1.0f;
+  if (a.arg_all) a.arg_all[o] = j;
+}
+
+template <int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC>
 hipError_t run(const SimArgs& a, hipStream_t st) {
-  using C = Cfg<D, SPLIT, NSUB, NWAVES, CPT, OCC, FG>;
+  using C = Cfg<D, SPLIT, NSUB, CPT, BITS, OCC>;
   const int64_t groups = a.n_heads >= 8 ? 8LL * ((a.n_heads + 7) / 8) : (int64_t)a.n_heads;
-  const int64_t blocks = groups * a.total_tiles;
-  if (blocks == 0) return hipSuccess;
-  if (a.counts != nullptr)
-    hipLaunchKernelGGL((sim_reduce_kernel<D, SPLIT, NSUB, NWAVES, CPT, OCC, FG, true>),
-                       dim3((unsigned)blocks), dim3(C::NT), 0, st, a);
-  else
-    hipLaunchKernelGGL((sim_reduce_kernel<D, SPLIT, NSUB, NWAVES, CPT, OCC, FG, false>),
-                       dim3((unsigned)blocks), dim3(C::NT), 0, st, a);
-  return hipGetLastError();
+  const int64_t rows = groups * a.total_tiles;
+  if (rows == 0) return hipSuccess;
+  int nseg = 1;
+  while (nseg < 16 && rows * nseg < 1024) ++nseg;
+  const dim3 block(C::NT), sweep((unsigned)(rows * nseg));
+  if (a.counts != nullptr) {
+    const int64_t words = (int64_t)a.n_heads * a.T;
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((words + 4 * kFlatThreads - 1) / (4 * kFlatThreads))),
+                       dim3(kFlatThreads), 0, st, reinterpret_cast<uint32_t*>(a.counts), words);
+    hipLaunchKernelGGL((sim_reduce_kernel<true, D, SPLIT, NSUB, CPT, BITS, OCC>), sweep, block, 0, st, a, nseg);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((sim_reduce_kernel<false, D, SPLIT, NSUB, CPT, BITS, OCC>), sweep, block, 0, st, a, nseg);
+  hipError_t e = hipGetLastError();
+  for (int h0 = 0; e == hipSuccess && h0 < a.n_heads; h0 += 65535) {
+    const int by = a.n_heads - h0 < 65535 ? a.n_heads - h0 : 65535;
+    hipLaunchKernelGGL(finish_kernel, dim3((unsigned)((a.T + kFlatThreads - 1) / kFlatThreads), (unsigned)by),
+                       dim3(kFlatThreads), 0, st, a, h0);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 }  // namespace
 
-// Tile shapes: (d, fp32 split, NSUB 32-row blocks per wave, waves per workgroup, 32-column
-// chunks per LDS tile, waves per SIMD, chunks merged before each running update: 1 or the
-// chunks per tile).  Overridable at build time for tuning sweeps.
+// Tile shapes: (d, fp32 split, 32-row blocks per wave, 32-column chunks per LDS tile, index bits
+// in the packed values).
 #ifndef TWINKV_CFG_BF16_128
-#define TWINKV_CFG_BF16_128 128, false, 3, 4, 4, 2, 4
+#define TWINKV_CFG_BF16_128 128, false, 2, 4, 6, 2
 #endif
 #ifndef TWINKV_CFG_BF16_64
-#define TWINKV_CFG_BF16_64 64, false, 4, 4, 2, 3, 1
+#define TWINKV_CFG_BF16_64 64, false, 2, 4, 4, 2
 #endif
 #ifndef TWINKV_CFG_F32_64
-#define TWINKV_CFG_F32_64 64, true, 1, 4, 4, 2, 1
+#define TWINKV_CFG_F32_64 64, true, 1, 4, 4, 2
 #endif
 #ifndef TWINKV_CFG_F32_128
-#define TWINKV_CFG_F32_128 128, true, 1, 4, 2, 2, 1
+#define TWINKV_CFG_F32_128 128, true, 1, 2, 4, 2
 #endif
 
 int sim_rows_per_block(int dtype, int d) {
-  if (dtype == 0 && d == 128) return Cfg<TWINKV_CFG_BF16_128>::RB;
-  if (dtype == 0 && d == 64) return Cfg<TWINKV_CFG_BF16_64>::RB;
-  if (dtype == 1 && d == 64) return Cfg<TWINKV_CFG_F32_64>::RB;
-  if (dtype == 1 && d == 128) return Cfg<TWINKV_CFG_F32_128>::RB;
+  if (d != 64 && d != 128) return 0;
+  if (dtype == 0) return 4 * 2 * 32;
+  if (dtype == 1) return 4 * 1 * 32;
   return 0;
 }
 
 int launch_sim_reduce(const SimArgs& a, int dtype, int d, void* stream) {
   hipStream_t st = (hipStream_t)stream;
+  if (a.counts == nullptr && !a.want_all) return launch_sim_retained(a, dtype, d, st);
   if (dtype == 0 && d == 128) return run<TWINKV_CFG_BF16_128>(a, st);
   if (dtype == 0 && d == 64) return run<TWINKV_CFG_BF16_64>(a, st);
   if (dtype == 1 && d == 64) return run<TWINKV_CFG_F32_64>(a, st);

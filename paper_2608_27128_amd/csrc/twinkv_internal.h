@@ -39,10 +39,18 @@ constexpr int kGroupAlign = TWINKV_GROUP_ALIGN;
 constexpr int kPermPad = kGroupAlign + kChunk;  // padding per (head, sequence) in the column lists
 constexpr int kFlagNonfinite = 1;
 
+// The sweep's candidates follow the S0 prefix counts in the workspace: `slots` = n_heads * PT
+// prefix counts, then from the next 256-byte boundary [2][n_heads][PT] 64-bit words (SimArgs::best).
+constexpr size_t candidates_offset(size_t slots) { return (4 * slots + 255) / 256 * 256; }
+inline unsigned long long* candidates_of(const int32_t* prank, int64_t slots) {
+  return reinterpret_cast<unsigned long long*>(
+      reinterpret_cast<char*>(const_cast<int32_t*>(prank)) + candidates_offset((size_t)slots));
+}
+
 // Workspace layout shared by the size query and the launchers.
 struct Layout {
   size_t seqtab = 0, rinv = 0, pcol = 0, rcol = 0, prank = 0, pmeta = 0, hilo = 0, pkeys = 0,
-         bbuf = 0, chunk_seq = 0, chunk_cnt = 0;
+         best = 0, bbuf = 0, chunk_seq = 0, chunk_cnt = 0;
   size_t total = 0;
 };
 
@@ -61,11 +69,16 @@ int launch_partition(const uint8_t* retained, const SeqInfo* seqtab, int n_heads
                      int64_t T, int64_t PT, int max_len, int32_t* pcol, float* rcol,
                      int32_t* prank, ProblemMeta* pmeta, int32_t* status, void* stream);
 
-// K1b: one pass over the keys after K1a: inverse l2 norm of every key (fp64 accumulation) to
-// rinv and to rcol at the key's column slot, the key copied to pkeys[h][PT][dcol] at that slot
-// (bf16; dcol = 2d bf16 hi/lo for fp32 keys, which also go to the row plane hilo
-// [n_heads][T][2d]); a non-finite key sets the problem's flag and status.  With copy_evicted
-// = 0 only the S0 columns are copied (sweeps over the retained columns alone).
+// K1b: one pass over the keys after K1a: r = 1 / ||k|| of every key (fp64 accumulation) to rinv, and
+// the column copy.  A non-finite key sets the problem's flag and status.
+// With copy_evicted (sweeps over all pairs): with g the power of two that brings ||g k|| into
+// (0.5, 1], r / g goes to rcol at the key's column slot, and g k to the slot's place in pkeys (bf16;
+// dcol = 2d bf16 hi/lo for fp32 keys): per problem, 32-slot chunk by chunk, 16-byte piece p of the
+// chunk's column c at byte 512 p + 16 c.  The padding of each list holds copies of its last key, and
+// the candidates at the tokens' slots (candidates_of) are cleared.
+// Without (sweeps over the S0 columns alone): r goes to rcol, and only S0 keys are copied, unscaled,
+// to pkeys[h][PT][dcol] (fp32 keys also go to the row plane hilo [n_heads][T][2d]); the S0 list's
+// last partly filled chunk holds copies of its last key.
 // Tokens one K1b workgroup prepares for this (dtype, d); sequence s owns workgroups
 // [seqtab[s].prep_blk0, seqtab[s].prep_blk0 + ceil(len / that)) of each head.
 int prepare_tokens_per_block(int dtype, int d);
@@ -116,9 +129,18 @@ struct SimArgs {
   int32_t* arg_all;
   float* best_ret;
   int32_t* arg_ret;
+  unsigned long long* best;  // [2][n_heads][PT] workspace (unused in count mode): the best candidate
+                             // of each slot over the S0 / evicted columns, value << 32 | ~slot
 };
 
-// Rows covered by one workgroup of the similarity kernel for this (dtype, d).
+// The sweep over the S0 columns alone (SimArgs::want_all = 0, no counts), and the rows one of its
+// workgroups covers for this (dtype, d).
+int launch_sim_retained(const SimArgs& a, int dtype, int d, void* stream);
+constexpr int sim_retained_rows_per_block(int dtype, int d) {
+  return dtype == 0 ? (d == 128 ? 384 : d == 64 ? 512 : 0) : (dtype == 1 && (d == 64 || d == 128) ? 128 : 0);
+}
+
+// Rows covered by one workgroup of the all-pairs kernel for this (dtype, d).
 int sim_rows_per_block(int dtype, int d);
 // K2: fused MFMA similarity with the two masked row max / argmax reductions, or (counts set)
 // the per-token twin counts of Eq. 2 over all columns.

@@ -1,0 +1,39 @@
+"""The pair sweep (every unordered pair once, reduced into both tokens) at the edges of its tiling:
+row blocks of 128 or 256 slots, 128-slot group alignment, 32-slot chunks, windows of 16 or 64
+chunks in the row direction, column segments (few row blocks) and the XCD-affine order (>= 8
+heads).  Scores and counts against the oracle; the S0-only sweep against the pair sweep."""
+import numpy as np
+import pytest
+
+from gpu_util import host, mask_to_device, to_device
+from paper_2608_27128_amd import binding, synth
+from test_gpu_parity import masks_for, run_and_check, small_spec
+from test_gpu_scorer import check_counts
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 32, 33, 127, 128, 129, 255, 256, 257, 385, 641]
+CASES = [
+    # (heads, lens, w, mask)
+    (1, EDGES, 0, "policy"),
+    (9, EDGES, 40, "policy"),
+    (2, [513, 2049 + 64], 7, "policy"),     # crosses a window of 64 (d = 128) and of 16 chunks
+    (1, [2500], 1200, "policy"),            # the window reaches over most row blocks
+    (2, [300, 640], 3, "one"),
+    (2, [300, 640], 3, "all"),
+]
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
+@pytest.mark.parametrize("H,lens,w,kind", CASES)
+def test_edges(H, lens, w, kind, d, dtype):
+    batch = synth.make_batch(small_spec(H, lens, d, dtype, w, 71 + len(lens), dup_frac=0.3))
+    gpu, _ = run_and_check(batch, w, kind, seed=5)
+    kt = to_device(batch.keys, dtype)
+    counts = host(binding.twin_counts(kt, 0.9, w, batch.cu_seqlens)["counts"])
+    check_counts(batch, counts, 0.9, w)
+    # the S0 columns alone give the same bits
+    rt = mask_to_device(masks_for(kind, batch, 5))
+    lean = binding.repair(kt, rt, batch.budget, 0.9, w, 2, 3, batch.cu_seqlens, want_all=False)
+    for k in ("best_ret", "arg_ret"):
+        assert np.array_equal(host(lean[k]), gpu[k]), k

@@ -48,6 +48,7 @@ constexpr int kSchedDsRead = 0x100;
 struct Place {
   int head, rb, len, n_ret, ret_chunks, total_chunks;
   int64_t colbase, rowbase;  // first slot in the column arrays, first token in the row arrays
+  int problem;               // head * n_seqs + sequence
   int64_t keybase;           // element offset of the sequence's first row key
 };
 // Workgroup k (of those of XCD x when there are >= 8 heads: heads h = x (mod 8) go to the XCD the
@@ -83,7 +84,8 @@ __device__ inline bool find_place(const SimArgs& a, int block, Place& pl, int& p
   pl.rb = local - (local / nb) * nb;
   const int seq = a.seqtab[lo].sorted_seq;
   const SeqInfo si = a.seqtab[seq];
-  const ProblemMeta pm = a.pmeta[pl.head * a.n_seqs + seq];
+  pl.problem = pl.head * a.n_seqs + seq;
+  const ProblemMeta pm = a.pmeta[pl.problem];
   pl.len = si.len;
   pl.n_ret = pm.n_ret;
   pl.ret_chunks = pm.ret_chunks;

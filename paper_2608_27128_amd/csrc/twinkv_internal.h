@@ -38,6 +38,7 @@ constexpr int kChunk = 32;           // columns per MFMA chunk (the 32x32x16 til
 constexpr int kGroupAlign = TWINKV_GROUP_ALIGN;
 constexpr int kPermPad = kGroupAlign + kChunk;  // padding per (head, sequence) in the column lists
 constexpr int kFlagNonfinite = 1;
+constexpr int kDoneShift = 8;  // flags >> kDoneShift: workgroups of the pair sweep that are done
 
 // The sweep's candidates follow the S0 prefix counts in the workspace: `slots` = n_heads * PT
 // prefix counts, then from the next 256-byte boundary [2][n_heads][PT] 64-bit words (SimArgs::best).
@@ -116,7 +117,7 @@ struct SimArgs {
   const int32_t* pcol;       // [n_heads][PT]
   const float* rcol;         // [n_heads][PT]
   const int32_t* prank;      // [n_heads][PT]: S0 positions before t
-  const ProblemMeta* pmeta;  // [n_heads * n_seqs]
+  ProblemMeta* pmeta;        // [n_heads * n_seqs]
   const SeqInfo* seqtab;     // [n_seqs]
   int n_heads, n_seqs;
   int64_t T, PT;
@@ -124,6 +125,7 @@ struct SimArgs {
   int want_all;              // also reduce over evicted columns (best_all / arg_all)
   float tau;                 // count mode: the twin threshold of Eq. 2
   int32_t* counts;           // non-null: count mode, [n_heads][T] twin counts (Eq. 2)
+  int max_len;               // longest sequence
   int total_tiles;           // row-block tiles of all sequences (sum of nb)
   float* best_all;
   int32_t* arg_all;

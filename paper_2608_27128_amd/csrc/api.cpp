@@ -250,6 +250,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   a.T = bt.T;
   a.PT = bt.PT;
   a.max_len = max_seq_len(cu, bt.n_seqs);
+  a.finish_len = 0;
   a.total_tiles = total_tiles;
   a.w = 0;
   a.want_all = 0;

@@ -260,11 +260,13 @@ __device__ inline void load_rows(const SimArgs& a, const Place& pl, int row0, in
   }
 }
 
-// Sequences of at most this many tokens get their results from the sweep itself, by the problem's last
-// workgroup, which saves the launch of finish_kernel (one fp32 head of 512 tokens, d = 64: 41.3 -> 38.4
-// us).  That workgroup works alone, with loads past the caches, so longer sequences are left to the
-// kernel: 8 heads of 1000 tokens take 51 us instead of 45, of 2000 tokens 81 instead of 47.
-constexpr int kFinishLen = 512;
+// In a batch of few problems, sequences of at most kFinishLen tokens get their results from the sweep
+// itself, by the problem's last workgroup, which saves the launch of finish_kernel (one fp32 head of
+// 512 tokens, d = 64: 41.3 -> 38.4 us).  That workgroup works alone, with loads past the caches, so
+// longer sequences are left to the kernel (8 heads of 1000 tokens take 51 us instead of 45, of 2000
+// tokens 81 instead of 47), and so are many problems (2048 of 95-137 tokens: 194 us instead of 186;
+// 288 of 395 tokens: 101 instead of 99).
+constexpr int kFinishLen = 512, kFinishProblems = 64;
 
 // Token i's candidates to its results (rowbase: its sequence's first token in the results).
 __device__ inline void finish_token(const SimArgs& a, int64_t colbase, int64_t rowbase, int i, int ret_pad) {
@@ -882,7 +884,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
     Place pd;
     int part;
     (void)find_place(b, block, pd, part);
-    if (pd.len > kFinishLen) return;
+    if (pd.len > b.finish_len) return;
     __syncthreads();
     int* const s_done = reinterpret_cast<int*>(smem);
     if (threadIdx.x == 0) {
@@ -909,7 +911,7 @@ __global__ __launch_bounds__(kFlatThreads) void clear_kernel(uint32_t* __restric
 }
 
 // The candidates of every token to its results: best_ret / arg_ret from plane 0 (S0 columns),
-// best_all / arg_all from both planes.  (Sequences of at most kFinishLen tokens are done already.)
+// best_all / arg_all from both planes.  (Sequences of at most finish_len tokens are done already.)
 __global__ __launch_bounds__(kFlatThreads) void finish_kernel(SimArgs a, int h0) {
   const int64_t t = (int64_t)blockIdx.x * kFlatThreads + threadIdx.x;
   if (t >= a.T) return;
@@ -920,14 +922,15 @@ __global__ __launch_bounds__(kFlatThreads) void finish_kernel(SimArgs a, int h0)
     if (a.seqtab[mid].start <= t) lo = mid; else hi = mid - 1;
   }
   const SeqInfo si = a.seqtab[lo];
-  if (si.len <= kFinishLen) return;
+  if (si.len <= a.finish_len) return;
   const ProblemMeta pm = a.pmeta[head * a.n_seqs + lo];
   finish_token(a, (int64_t)head * a.PT + si.perm_off, (int64_t)head * a.T + si.start, (int)(t - si.start),
                pm.ret_chunks * kChunk);
 }
 
 template <int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC>
-hipError_t run(const SimArgs& a, hipStream_t st) {
+hipError_t run(SimArgs a, hipStream_t st) {
+  a.finish_len = (int64_t)a.n_heads * a.n_seqs <= kFinishProblems ? kFinishLen : 0;
   using C = Cfg<D, SPLIT, NSUB, CPT, BITS, OCC>;
   const int64_t groups = a.n_heads >= 8 ? 8LL * ((a.n_heads + 7) / 8) : (int64_t)a.n_heads;
   const int64_t rows = groups * a.total_tiles;
@@ -943,7 +946,7 @@ hipError_t run(const SimArgs& a, hipStream_t st) {
     return hipGetLastError();
   }
   hipLaunchKernelGGL((sim_reduce_kernel<false, D, SPLIT, NSUB, CPT, BITS, OCC>), sweep, block, 0, st, a, nseg);
-  if (a.max_len <= kFinishLen) return hipGetLastError();
+  if (a.max_len <= a.finish_len) return hipGetLastError();
   hipError_t e = hipGetLastError();
   for (int h0 = 0; e == hipSuccess && h0 < a.n_heads; h0 += 65535) {
     const int by = a.n_heads - h0 < 65535 ? a.n_heads - h0 : 65535;

@@ -126,6 +126,7 @@ struct SimArgs {
   float tau;                 // count mode: the twin threshold of Eq. 2
   int32_t* counts;           // non-null: count mode, [n_heads][T] twin counts (Eq. 2)
   int max_len;               // longest sequence
+  int finish_len;            // (set by the launcher) the sweep writes the results of sequences this short
   int total_tiles;           // row-block tiles of all sequences (sum of nb)
   float* best_all;
   int32_t* arg_all;

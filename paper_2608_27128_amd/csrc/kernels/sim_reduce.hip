@@ -268,8 +268,11 @@ __device__ inline void load_rows(const SimArgs& a, const Place& pl, int row0, in
 // 288 of 395 tokens: 101 instead of 99).
 constexpr int kFinishLen = 512, kFinishProblems = 64;
 
-// Token i's candidates to its results (rowbase: its sequence's first token in the results).
-__device__ inline void finish_token(const SimArgs& a, int64_t colbase, int64_t rowbase, int i, int ret_pad) {
+// Token i's candidates to its results (rowbase: its sequence's first token in the results; nslots: the
+// slots of its problem's list).  A key with infinite elements makes NaN of a dropped block's zero r', in
+// the row direction also of the zeros past the list's end: a candidate there names no token.
+__device__ inline void finish_token(const SimArgs& a, int64_t colbase, int64_t rowbase, int i, int ret_pad,
+                                    int nslots) {
   const int r0 = a.prank[colbase + i], r1 = a.prank[colbase + i + 1];
   const int slot = r1 > r0 ? r0 : ret_pad + (i - r0);
   const int64_t o = rowbase + i;
@@ -281,8 +284,9 @@ __device__ inline void finish_token(const SimArgs& a, int64_t colbase, int64_t r
   const u64 ke = __hip_atomic_load(best + (int64_t)a.n_heads * a.PT + slot, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t vr = (uint32_t)(kr >> 32), ve = (uint32_t)(ke >> 32);
-  const int jr = vr >= kValidMin ? pc[~(uint32_t)kr] : -1;
-  const int je = ve >= kValidMin ? pc[~(uint32_t)ke] : -1;
+  const uint32_t sr = ~(uint32_t)kr, se = ~(uint32_t)ke;
+  const int jr = vr >= kValidMin && sr < (uint32_t)nslots ? pc[sr] : -1;
+  const int je = ve >= kValidMin && se < (uint32_t)nslots ? pc[se] : -1;
   if (a.best_ret) a.best_ret[o] = jr >= 0 ? similarity(vr, ri) : -1.0f;
   if (a.arg_ret) a.arg_ret[o] = jr;
   const bool take_r = jr >= 0 && (je < 0 || vr > ve || (vr == ve && jr < je));
@@ -896,7 +900,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
     if (*s_done != (pd.total_chunks * kChunk + C::RB - 1) / C::RB * nseg - 1) return;
 #pragma unroll 2
     for (int i = threadIdx.x; i < pd.len; i += C::NT)
-      finish_token(b, pd.colbase, pd.rowbase, i, pd.ret_chunks * kChunk);
+      finish_token(b, pd.colbase, pd.rowbase, i, pd.ret_chunks * kChunk, pd.total_chunks * kChunk);
   }
 }
 
@@ -925,7 +929,7 @@ __global__ __launch_bounds__(kFlatThreads) void finish_kernel(SimArgs a, int h0)
   if (si.len <= a.finish_len) return;
   const ProblemMeta pm = a.pmeta[head * a.n_seqs + lo];
   finish_token(a, (int64_t)head * a.PT + si.perm_off, (int64_t)head * a.T + si.start, (int)(t - si.start),
-               pm.ret_chunks * kChunk);
+               pm.ret_chunks * kChunk, pm.total_chunks * kChunk);
 }
 
 template <int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC>

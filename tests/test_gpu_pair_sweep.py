@@ -37,3 +37,29 @@ def test_edges(H, lens, w, kind, d, dtype):
     lean = binding.repair(kt, rt, batch.budget, 0.9, w, 2, 3, batch.cu_seqlens, want_all=False)
     for k in ("best_ret", "arg_ret"):
         assert np.array_equal(host(lean[k]), gpu[k]), k
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
+@pytest.mark.parametrize("with_s0", [False, True])
+def test_infinite_element_names_only_tokens(d, dtype, with_s0):
+    """With positive keys, an infinite element gives +Inf against every token and NaN against the
+    zeros that fill the last tile past the list's end.  The scores of that problem are unspecified, but
+    a reported position is one of its tokens, whatever the workspace holds past its column list."""
+    import torch
+    lens = [40, 300, 33]
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    g = np.random.default_rng(d + with_s0)
+    keys = (0.5 + g.random((2, cu[-1], d))).astype(np.float32)
+    for h, s in ((0, 0), (1, 1), (1, 2)):
+        keys[h, cu[s] + 5, 7] = np.inf
+    kt = torch.from_numpy(keys).cuda()
+    kt = kt.to(torch.bfloat16) if dtype == "bf16" else kt
+    ret = torch.from_numpy((g.random((2, cu[-1])) < 0.5).astype(np.uint8)).cuda() if with_s0 else None
+    nb = binding.workspace_bytes(binding.OP_NN_SCORES, 0 if dtype == "bf16" else 1, d, 2, cu)
+    ws = torch.full((nb,), 0x7F, dtype=torch.uint8, device="cuda")
+    out = {k: host(v) for k, v in binding.nn_scores(kt, ret, 3, cu, workspace=ws).items()}
+    assert list(out["status"]) == [2, 0, 0, 0, 2, 2]
+    for k in ("arg_all", "arg_ret") if with_s0 else ("arg_all",):
+        for s, n in enumerate(lens):
+            a = out[k][:, cu[s]:cu[s + 1]]
+            assert a.min() >= -1 and a.max() < n, (k, s)

@@ -43,9 +43,8 @@
 //    the row direction's serial maxima (NSUB 2 and 4, both slower); with three the 2 x 16 running
 //    maxima per row block do not fit.
 //  * Products of bf16 values are exact in fp32; accumulation is fp32.  fp32 keys use the
-//    split k = hi + lo (bf16 each) and the sums hi.hi + (lo.hi + hi.lo), the two cross sums
-//    in accumulators of their own: swapping the two tokens swaps them, and their sum is the
-//    same.
+//    split k = hi + lo (bf16 each).  The cross sums lo.hi and hi.lo have accumulators of their own:
+//    swapping the two tokens swaps them, and their sum, from which the hi.hi chain goes on, is the same.
 //  * Chunks that hold pairs inside the window, the rows' own chunks and padding are dropped by
 //    scalar masks in the sweep (their r' and the bias become 0, so x stays below any candidate);
 //    a masked pass after the sweep redoes those that hold real pairs, with the window tested per
@@ -609,7 +608,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
                         int buf3, int pbuf3) {
     // VALU instructions placed beside each MFMA: one block's reductions over its MFMAs
     constexpr int VALU_PER_MFMA =
-        ((COUNT ? 54 : 86) + (SPLIT ? 32 : 0) + C::MFMAS - 1) / C::MFMAS;
+        ((COUNT ? 54 : 86) + (SPLIT ? 16 : 0) + C::MFMAS - 1) / C::MFMAS;
     const uint32_t fbase = lane_base + stage;
     const char* st = smem + stage;
     bf16x8 fb[C::UF];
@@ -628,19 +627,24 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
 #pragma unroll
       for (int s = 0; s < NSUB; ++s) {
         f32x16 y = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f32x16 yp = y, yq = y;
+        f32x16 yq = y;
         const bool pre = (s == NSUB - 1) && (kc + 1 < CPT);
 #pragma unroll
         for (int t = 0; t < C::UF; ++t) {
           if constexpr (!SPLIT) {
             y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
           } else if (t < G) {
-            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
-            yp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][G + t], fb[t], yp, 0, 0, 0);
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][G + t], fb[t], y, 0, 0, 0);
+            yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[G + t], yq, 0, 0, 0);
+            if (t == G - 1) {
+#pragma unroll
+              for (int v = 0; v < 16; ++v) y[v] += yq[v];
+            }
           } else {
-            yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t - G], fb[t], yq, 0, 0, 0);
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t - G], fb[t - G], y, 0, 0, 0);
           }
-          if (pre) fb[t] = read_frag(fbase, t, kc + 1);
+          const int done = !SPLIT ? t : t < G ? G + t : t - G;
+          if (pre) fb[done] = read_frag(fbase, done, kc + 1);
         }
         if (s == 0) {
           // the pending chunk: the previous chunk of this tile, or the last of the previous tile
@@ -662,12 +666,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
           col_emit(cres, kc == 0 ? pbuf3 : buf3, kc == 0 ? CPT - 1 : kc - 1);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (SPLIT) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) x[v] = y[v] + (yp[v] + yq[v]);
-        } else {
-          x = y;
-        }
+        x = y;
       }
       pacc = x;
       prl = rl;
@@ -807,21 +806,21 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
         cb.b[s] = 0u;
         if (cgrp == grp && gc < row0 / kChunk + s) continue;  // the other half of the triangle
         f32x16 y = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        f32x16 yp = y, yq = y;
+        f32x16 yq = y;
 #pragma unroll
         for (int t = 0; t < C::UF; ++t) {
           if constexpr (!SPLIT) {
             y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
           } else if (t < G) {
-            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[t], y, 0, 0, 0);
-            yp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][G + t], fb[t], yp, 0, 0, 0);
-          } else {
-            yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t - G], fb[t], yq, 0, 0, 0);
-          }
-        }
-        if constexpr (SPLIT) {
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][G + t], fb[t], y, 0, 0, 0);
+            yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t], fb[G + t], yq, 0, 0, 0);
+            if (t == G - 1) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) y[v] = y[v] + (yp[v] + yq[v]);
+              for (int v = 0; v < 16; ++v) y[v] += yq[v];
+            }
+          } else {
+            y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag[s][t - G], fb[t - G], y, 0, 0, 0);
+          }
         }
 #pragma unroll
         for (int v4 = 0; v4 < 4; ++v4) {

@@ -16,7 +16,7 @@
 //    update per chunk the code is the register (4 bits, quantum 2^-18 of the scaled similarity); with
 //    one per tile of 4 chunks it also holds the chunk's place in the tile (6 bits, quantum 2^-16), so
 //    the compare-and-select of the running update runs once per 128 columns.
-//  * fp32 keys use the bf16 split k = hi + lo and three products (hi.hi, lo.hi, hi.lo).
+//  * fp32 keys use the bf16 split k = hi + lo and three products (lo.hi, hi.lo, hi.hi).
 // The sweep of all pairs, which reduces into both tokens of a pair, was slower here: 288 heads x 16k
 // in three levels 12.0 -> 12.4 ms, 96 problems of 150-3000 tokens at d = 64 98 -> 101 us.
 #include <type_traits>
@@ -49,41 +49,42 @@ struct Cfg {
   static constexpr int LOADS_PER_WAVE = TN * PPC / (kWaves * 64);  // 1-KB direct loads
   // VALU instructions the schedule places beside each MFMA: one chunk's epilogue (about 40
   // with the tile merge, 48 with a running update per chunk) over its MFMAs
-  static constexpr int VALU_PER_MFMA = ((FG > 1 ? 40 : 48) + (SPLIT ? 32 : 0) + MFMAS - 1) / MFMAS;
+  static constexpr int VALU_PER_MFMA = ((FG > 1 ? 40 : 48) + (SPLIT ? 16 : 0) + MFMAS - 1) / MFMAS;
   static_assert((TN * PPC) % (kWaves * 64) == 0, "tile copy must divide evenly");
   static_assert(TN % 64 == 0 && TN <= kWaves * 64, "the inverse norms move in 64-column pieces");
   static_assert(2 * STAGE <= 160 * 1024 / WG_PER_CU,
                 "LDS of WG_PER_CU workgroups must fit one CU");
 };
 
-// The products of one 32 x 32 block.  fp32 keys hold fragments [hi | lo] on both sides and keep the two
-// cross sums in accumulators of their own, as the all-pairs sweep does: the same bits for a pair.
+// The products of one 32 x 32 block.  fp32 keys hold fragments [hi | lo] on both sides; the two cross
+// sums have accumulators of their own and their sum starts the hi.hi chain, as in the all-pairs sweep:
+// the same bits for a pair, whichever of its tokens is the row.  (Summed after the chains, twice the
+// adds: 64 heads x 16k 5.66 ms at d = 128 and 3.10 at d = 64, against 5.46 and 2.95 here; all products
+// in one chain take 5.33 and 2.80, but their bits depend on the order of the two tokens.)
 template <int D, bool SPLIT>
 struct Block {
   static constexpr int G = D / 16;
-  f32x16 y, yp, yq;
+  f32x16 y, yq;
   __device__ Block() {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) y[v] = yp[v] = yq[v] = 0.0f;
+    for (int v = 0; v < 16; ++v) y[v] = yq[v] = 0.0f;
   }
+  // step t of UF (one fragment of the column is done after it: done(t))
+  static __device__ constexpr int done(int t) { return !SPLIT ? t : t < G ? G + t : t - G; }
   template <int UF>
-  __device__ void step(const bf16x8& col, const bf16x8 (&row)[UF], int t) {
+  __device__ void step(const bf16x8 (&col)[UF], const bf16x8 (&row)[UF], int t) {
     if constexpr (!SPLIT) {
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col, row[t], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col[t], row[t], y, 0, 0, 0);
     } else if (t < G) {
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col, row[t], y, 0, 0, 0);
-      yp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col, row[G + t], yp, 0, 0, 0);
-    } else {
-      yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col, row[t - G], yq, 0, 0, 0);
-    }
-  }
-  __device__ f32x16 sum() const {
-    f32x16 x = y;
-    if constexpr (SPLIT) {
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col[t], row[G + t], y, 0, 0, 0);
+      yq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col[G + t], row[t], yq, 0, 0, 0);
+      if (t == G - 1) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) x[v] = y[v] + (yp[v] + yq[v]);
+        for (int v = 0; v < 16; ++v) y[v] += yq[v];
+      }
+    } else {
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col[t - G], row[t - G], y, 0, 0, 0);
     }
-    return x;
   }
 };
 
@@ -362,9 +363,10 @@ __global__ __launch_bounds__(kWaves * 64, (Cfg<D, SPLIT, NSUB, CPT, OCC, FG>::WG
       Block<D, SPLIT> b0;
 #pragma unroll
       for (int t = 0; t < C::UF; ++t) {
-        b0.step(fc[t], bfrag[0], t);
+        b0.step(fc, bfrag[0], t);
         if (pre0)
-          fc[t] = *reinterpret_cast<const bf16x8*>(st + (kc + 1) * C::CHUNK_BYTES + aoff[t]);
+          fc[Block<D, SPLIT>::done(t)] = *reinterpret_cast<const bf16x8*>(
+              st + (kc + 1) * C::CHUNK_BYTES + aoff[Block<D, SPLIT>::done(t)]);
       }
       // the pending chunk: the previous chunk of this tile, or the last of the previous tile
       reduce_into(pacc, prv, pgc, kc == 0 ? CPT - 1 : kc - 1, NSUB - 1, pmask);
@@ -376,16 +378,17 @@ __global__ __launch_bounds__(kWaves * 64, (Cfg<D, SPLIT, NSUB, CPT, OCC, FG>::WG
         if (i < 4 || pre0) __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 1, 0);
         __builtin_amdgcn_sched_group_barrier(kSchedValu, C::VALU_PER_MFMA, 0);
       }
-      f32x16 x = b0.sum();
+      f32x16 x = b0.y;
 #pragma unroll
       for (int s = 1; s < NSUB; ++s) {
         Block<D, SPLIT> bs;
         const bool pre = (s == NSUB - 1) && (kc + 1 < CPT);
 #pragma unroll
         for (int t = 0; t < C::UF; ++t) {
-          bs.step(fc[t], bfrag[s], t);
+          bs.step(fc, bfrag[s], t);
           if (pre)
-            fc[t] = *reinterpret_cast<const bf16x8*>(st + (kc + 1) * C::CHUNK_BYTES + aoff[t]);
+            fc[Block<D, SPLIT>::done(t)] = *reinterpret_cast<const bf16x8*>(
+              st + (kc + 1) * C::CHUNK_BYTES + aoff[Block<D, SPLIT>::done(t)]);
         }
         reduce_into(x, rcur, gc, kc, s - 1, mask_of(s - 1));
         if (kc == CPT - 1) flush(s - 1, c0);
@@ -395,7 +398,7 @@ __global__ __launch_bounds__(kWaves * 64, (Cfg<D, SPLIT, NSUB, CPT, OCC, FG>::WG
           if (pre) __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 1, 0);
           __builtin_amdgcn_sched_group_barrier(kSchedValu, C::VALU_PER_MFMA, 0);
         }
-        x = bs.sum();
+        x = bs.y;
       }
       pacc = x;
 #pragma unroll
@@ -511,8 +514,8 @@ __global__ __launch_bounds__(kWaves * 64, (Cfg<D, SPLIT, NSUB, CPT, OCC, FG>::WG
       }
       Block<D, SPLIT> b;
 #pragma unroll
-      for (int t = 0; t < C::UF; ++t) b.step(af[t], bfrag[s], t);
-      const f32x16 x = b.sum();
+      for (int t = 0; t < C::UF; ++t) b.step(af, bfrag[s], t);
+      const f32x16 x = b.y;
       const int i = wrow0 + s * 32 + l32;
       uint32_t best = 0u;
       // column of slot v, relative to the first excluded column of this row's range

@@ -242,10 +242,7 @@ __global__ __launch_bounds__(256) void prepare_keys_kernel(
   constexpr int DCOL = F32 ? 2 * D : D;
   static_assert(LPT <= 64 && (64 % LPT) == 0, "a key must fit inside one wave");
   const int64_t h = h0 + (int64_t)blockIdx.y;
-  // consecutive workgroups go round the 8 XCDs: each XCD takes a run of the head's tokens, so that
-  // the lines two neighbours share meet in one L2
-  const int per_xcd = (int)gridDim.x >> 3;
-  const int bx = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+  const int bx = prep_block((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, total_blocks);
   if (bx >= total_blocks) return;
   int lo = 0, hi = n_seqs - 1;  // the last sequence whose first workgroup is <= bx
   while (lo < hi) {
@@ -444,7 +441,7 @@ hipError_t run_prepare(const void* keys, int n_heads, int64_t T, int64_t hs, int
   for (int h0 = 0; h0 < n_heads; h0 += 65535) {  // heads along y, in slices the grid holds
     const int by = n_heads - h0 < 65535 ? n_heads - h0 : 65535;
     hipLaunchKernelGGL((prepare_keys_kernel<D, F32, LEVELS, ALL>),
-                       dim3((unsigned)(total_blocks + 7) / 8 * 8, (unsigned)by), dim3(256), 0, st,
+                       dim3((unsigned)prep_grid(total_blocks), (unsigned)by), dim3(256), 0, st,
                        (const uint8_t*)keys, T, hs * ESZ, ts * ESZ, PT, retained, prank, pmeta,
                        seqtab, n_seqs, rinv, rcol, hilo, pkeys, status, h0,
                        LEVELS ? nullptr : candidates_of(prank, (int64_t)n_heads * PT),

@@ -117,14 +117,17 @@ __global__ __launch_bounds__(NT) void partition_kernel(
 // Sequences of at most kShortLen tokens: all of a thread's mask bytes in one round of loads, the
 // waves' ballot counts scanned by one wave, two barriers in all (the slab-by-slab kernel takes two
 // per 256 tokens: 9.0 against 5.5 us for 12 x 8 problems of 150 to 3000 tokens, where it is one
-// of few short kernels in a row).
+// of few short kernels in a row).  ROUNDS of 256 tokens each: 16, or 4 where no sequence is longer, so
+// that many short problems don't pay for empty rounds (2048 problems of 240-300 tokens: 6.4 us with 16,
+// 5.6 with 4, 5.7 slab by slab).
 constexpr int kShortLen = 4096;
+template <int ROUNDS>
 __global__ __launch_bounds__(256) void partition_short_kernel(
     const uint8_t* __restrict__ retained, const SeqInfo* __restrict__ seqtab, int n_seqs,
     int64_t T, int64_t PT, int32_t* __restrict__ pcol, float* __restrict__ rcol,
     int32_t* __restrict__ prank, ProblemMeta* __restrict__ pmeta, int32_t* __restrict__ status) {
-  constexpr int U = kShortLen / 256;
-  static_assert(U * 4 == 64, "one count per lane of the scanning wave");
+  constexpr int U = ROUNDS;
+  static_assert(U * 4 <= 64, "one count per lane of the scanning wave");
   __shared__ int s_cnt[U * 4], s_pre[U * 4], s_total;
   const int q = blockIdx.x;
   const int h = q / n_seqs;
@@ -149,14 +152,14 @@ __global__ __launch_bounds__(256) void partition_short_kernel(
   }
   __syncthreads();
   if (wv == 0) {
-    const int v = s_cnt[lane];
+    const int v = lane < U * 4 ? s_cnt[lane] : 0;
     int inc = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const int y = __shfl_up(inc, off);
       if (lane >= off) inc += y;
     }
-    s_pre[lane] = inc - v;
+    if (lane < U * 4) s_pre[lane] = inc - v;
     if (lane == 63) s_total = inc;
   }
   __syncthreads();
@@ -489,8 +492,12 @@ int launch_partition(const uint8_t* retained, const SeqInfo* seqtab, int n_heads
     hipLaunchKernelGGL(partition_kernel<1024>, dim3((unsigned)P), dim3(1024), 0,
                        (hipStream_t)stream, retained, seqtab, n_seqs, T, PT, pcol, rcol, prank,
                        pmeta, status);
+  else if (max_len > kShortLen / 4)
+    hipLaunchKernelGGL(partition_short_kernel<kShortLen / 256>, dim3((unsigned)P), dim3(256), 0,
+                       (hipStream_t)stream, retained, seqtab, n_seqs, T, PT, pcol, rcol, prank,
+                       pmeta, status);
   else
-    hipLaunchKernelGGL(partition_short_kernel, dim3((unsigned)P), dim3(256), 0,
+    hipLaunchKernelGGL(partition_short_kernel<kShortLen / 1024>, dim3((unsigned)P), dim3(256), 0,
                        (hipStream_t)stream, retained, seqtab, n_seqs, T, PT, pcol, rcol, prank,
                        pmeta, status);
   return hipGetLastError();

@@ -439,7 +439,7 @@ def sweep_bench(args, sp, keys, dev) -> int:
         "grid_ms_one_pass_per_budget": ms_sep,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                     "kernel": "sim_retained_kernel (3 launches, one per level group)",
+                     "kernel": "sim_rect_kernel (3 launches, one per level group)",
                      "kernel_ms": k2_ms, "flops_per_launch": flops},
     }
     print(json.dumps(result), flush=True)
@@ -613,7 +613,7 @@ def main() -> int:
                      "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                      "traffic": profiled_traffic(sp.name, "repair_pass" if args.path == "repair"
                                                  else f"{args.path}_pass"),
-                     "kernel": "sim_retained_kernel" if args.path == "repair_s0" else "sim_reduce_kernel",
+                     "kernel": "sim_rect_kernel" if args.path == "repair_s0" else "sim_reduce_kernel",
                      "kernel_ms": k2_ms,
                      "kernel_ms_median": float(np.median(k2_each)),
                      "kernel_ms_min": float(np.min(k2_each)),

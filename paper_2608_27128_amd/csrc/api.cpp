@@ -153,6 +153,36 @@ std::vector<SeqInfo> seq_table(const int64_t* cu, int n_seqs, const int64_t* bud
   return tab;
 }
 
+}  // namespace
+
+// The pair sweep does half the products, but pays per problem: its lists are padded to whole groups, a
+// row block of a short list is half idle, its candidates are merged through memory and finished by a
+// kernel of their own, and its copy is written piece by piece.  With many short problems in flight the
+// full rectangle is faster.  The lines lie where the two measured the same over 1200 random batches (1 to
+// 18000 problems, 1 to 12000 tokens, ragged and even); with few problems the pair sweep wins at every
+// length, because it cuts a problem's columns into segments.  Rectangle / pair sweep, us a call:
+// repair of bf16 keys, d = 128, 1024 problems of 160-200 tokens 91 / 132, of 560-700 264 / 386, of
+// 1600-2000 1115 / 1060; 128 problems of 560-700 tokens 66 / 89; d = 64, 4096 of 410-512 448 / 565, 128 of
+// 410-512 63 / 51, 128 of 6400-8000 1040 / 918; counts, d = 128, 1024 of 100-128 57 / 71, of 800-1000
+// 378 / 318; repair of fp32 keys, d = 64, 4096 of 100-128 216 / 266.
+Sweep sweep_for(int dtype, int d, bool counts, int n_heads, int n_seqs, const int64_t* cu) {
+  struct Short {
+    int problems;     // at least so many of them
+    int mean_tokens;  // of at most so many tokens, in the mean over the tokens (the work goes by it)
+  };
+  const Short at = dtype == TWINKV_BF16
+                       ? (d == 128 ? (counts ? Short{96, 256} : Short{96, 1600})
+                                   : (counts ? Short{96, 300} : Short{160, 2500}))
+                       : (d == 128 ? (counts ? Short{96, 100} : Short{48, 100})
+                                   : (counts ? Short{48, 100} : Short{48, 300}));
+  if ((int64_t)n_heads * n_seqs < at.problems) return kSweepPairs;
+  int64_t squares = 0;
+  for (int s = 0; s < n_seqs; ++s) squares += (cu[s + 1] - cu[s]) * (cu[s + 1] - cu[s]);
+  return squares <= at.mean_tokens * cu[n_seqs] ? kSweepAll : kSweepPairs;
+}
+
+namespace {
+
 int hip_status(int e) { return e == 0 ? TWINKV_OK : TWINKV_E_HIP; }
 
 int max_seq_len(const int64_t* cu, int n_seqs) {
@@ -191,12 +221,12 @@ struct Prepared {
 int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const int64_t* cu,
                    const int64_t* budget, int64_t head_stride, int64_t token_stride,
                    const uint8_t* retained, int32_t* status, char* ws, const Layout& L,
-                   bool copy_evicted, void* stream, Prepared& P, bool key_prep = true) {
+                   Sweep sweep, void* stream, Prepared& P, bool key_prep = true) {
   int total_tiles = 0;
-  // the rows of the all-pairs sweep are slots of the column list, counted at its largest padding
-  // (both groups end with a partly filled unit); those of the S0 sweep are tokens
-  const int rpb = copy_evicted ? sim_rows_per_block(dtype, d) : sim_retained_rows_per_block(dtype, d);
-  const int row_pad = copy_evicted ? kPermPad - 2 : 0;
+  // the rows of the pair sweep are slots of the column list, counted at its largest padding
+  // (both groups end with a partly filled unit); those of the rectangles are tokens
+  const int rpb = sim_rows_per_block(sweep, dtype, d);
+  const int row_pad = sweep == kSweepPairs ? kPermPad - 2 : 0;
   int64_t prep_blocks = 0;
   std::vector<SeqInfo> tab = seq_table(cu, bt.n_seqs, budget, rpb, total_tiles,
                                        prepare_tokens_per_block(dtype, d), &prep_blocks, row_pad);
@@ -224,7 +254,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   if (key_prep) {
     e = launch_prepare_keys(keys, dtype, d, bt.n_heads, bt.T, head_stride, token_stride, bt.PT,
                             (int)prep_blocks, retained, prank, pmeta, dtab, bt.n_seqs, rinv, rcol,
-                            hilo, pkeys, status, copy_evicted ? 1 : 0, stream);
+                            hilo, pkeys, status, sweep, stream);
     if (e) return hip_status(e);
   }
 
@@ -253,7 +283,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   a.finish_len = 0;
   a.total_tiles = total_tiles;
   a.w = 0;
-  a.want_all = 0;
+  a.sweep = sweep;
   a.tau = 0.0f;
   a.counts = nullptr;
   a.best_all = nullptr;
@@ -265,13 +295,12 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
 }
 
 // K2 on prepared keys.
-int sim_scores(const Batch& bt, int dtype, int d, int w, bool want_all, float* best_all,
-               int32_t* arg_all, float* best_ret, int32_t* arg_ret, float tau, int32_t* counts,
-               Prepared& P, void* stream) {
+int sim_scores(const Batch& bt, int dtype, int d, int w, float* best_all, int32_t* arg_all,
+               float* best_ret, int32_t* arg_ret, float tau, int32_t* counts, Prepared& P,
+               void* stream) {
   SimArgs a = P.args;
   // |i - j| <= T - 1 inside any sequence, so any w >= T behaves like w = T.
   a.w = (int)std::min<int64_t>(w, std::max<int64_t>(bt.T, 1));
-  a.want_all = want_all ? 1 : 0;
   a.tau = tau;
   a.counts = counts;
   a.best_all = best_all;
@@ -293,13 +322,14 @@ int run_scores(const void* keys, int dtype, int d, const Batch& bt, const int64_
                bool want_all, void* stream, SeqInfo** seqtab_dev, float tau = 0.0f,
                int32_t* counts = nullptr) {
   Prepared P;
+  const Sweep sweep =
+      want_all ? sweep_for(dtype, d, counts != nullptr, bt.n_heads, bt.n_seqs, cu) : kSweepRetained;
   int rc = prepare_scores(keys, dtype, d, bt, cu, budget, head_stride, token_stride, retained,
-                          status, ws, L, want_all, stream, P);
+                          status, ws, L, sweep, stream, P);
   if (rc != TWINKV_OK) return rc;
   *seqtab_dev = P.seqtab;
   if ((rc = record(g_sim_start, stream)) != TWINKV_OK) return rc;
-  rc = sim_scores(bt, dtype, d, w, want_all, best_all, arg_all, best_ret, arg_ret, tau, counts, P,
-                  stream);
+  rc = sim_scores(bt, dtype, d, w, best_all, arg_all, best_ret, arg_ret, tau, counts, P, stream);
   if (rc != TWINKV_OK) return rc;
   return record(g_sim_stop, stream);
 }
@@ -630,7 +660,7 @@ int twinkv_nn_scores_levels(const void* keys, int dtype, int d, int n_heads, int
     if (launch_select_level(level, mask, n, sel, n_levels, stream) != 0) return TWINKV_E_HIP;
     rc = prepare_scores(keys, dtype, d, bt, cu_seqlens, nullptr, head_stride, token_stride, mask,
                         g == 0 ? status : nullptr, base + LL.per * (size_t)g, L,
-                        /*copy_evicted=*/false, stream, P[g], /*key_prep=*/false);
+                        kSweepRetained, stream, P[g], /*key_prep=*/false);
     if (rc != TWINKV_OK) return rc;
   }
   {
@@ -652,8 +682,8 @@ int twinkv_nn_scores_levels(const void* keys, int dtype, int d, int n_heads, int
   }
   if ((rc = record(g_sim_start, stream)) != TWINKV_OK) return rc;
   for (int g = 0; g < LL.groups; ++g) {
-    rc = sim_scores(bt, dtype, d, w, /*want_all=*/false, nullptr, nullptr, gbest + g * n,
-                    garg + g * n, 0.0f, nullptr, P[g], stream);
+    rc = sim_scores(bt, dtype, d, w, nullptr, nullptr, gbest + g * n, garg + g * n, 0.0f, nullptr,
+                    P[g], stream);
     if (rc != TWINKV_OK) return rc;
   }
   if ((rc = record(g_sim_stop, stream)) != TWINKV_OK) return rc;

@@ -230,14 +230,15 @@ __device__ inline void prep_store16(char* p, uint4 x) {
 // LEVELS: the groups of nested retained sets in one pass (PrepLevels): each token goes to
 // the column list of its own group, whose arrays lie group_stride bytes after the previous
 // group's; rinv (and the fp32 row plane) is written once for all groups.  Without LEVELS,
-// `retained` splits the positions into the one S0 list and the evicted list.
+// `retained` splits the positions into the one S0 list and the evicted list.  ALL: the copy of
+// kSweepPairs; without it, evicted columns are copied as copy_evicted says.
 template <int D, bool F32, bool LEVELS, bool ALL>
 __global__ __launch_bounds__(256) void prepare_keys_kernel(
     const uint8_t* __restrict__ keys, int64_t T, int64_t hs_bytes, int64_t ts_bytes, int64_t PT,
     const uint8_t* __restrict__ retained, const int32_t* __restrict__ prank,
     ProblemMeta* __restrict__ pmeta, const SeqInfo* __restrict__ seqtab, int n_seqs,
     float* __restrict__ rinv, float* __restrict__ rcol, uint16_t* __restrict__ hilo,
-    uint16_t* __restrict__ pkeys, int32_t* __restrict__ status, int h0,
+    uint16_t* __restrict__ pkeys, int32_t* __restrict__ status, int h0, int copy_evicted,
     unsigned long long* __restrict__ best, int64_t plane, int total_blocks, PrepLevels lv) {
   constexpr int ESZ = F32 ? 4 : 2;
   constexpr int LPT = D * ESZ / 16;
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(256) void prepare_keys_kernel(
     }
     const int pr = byte_offset(prank, goff)[base + (valid ? tl : 0)];
     const int p = r ? pr : ret_cols + ((valid ? tl : 0) - pr);
-    const bool copy = valid && (r || ALL);  // evicted columns only for all-keys sweeps
+    const bool copy = valid && (r || ALL || copy_evicted);  // evicted columns only for all-keys sweeps
     // The last column of a group fills the rest of the group's padding (S0: up to kGroupAlign
     // columns, evicted: its 32-column chunk) with copies of itself (key and r'; the position
     // list keeps -1 there), so the padding holds only exact ties of a real column.
@@ -361,9 +362,11 @@ __global__ __launch_bounds__(256) void prepare_keys_kernel(
         plo.x = ls[0] | ((uint32_t)ls[1] << 16);
         plo.y = ls[2] | ((uint32_t)ls[3] << 16);
         if constexpr (!ALL) {
-          uint16_t* plane_row = hilo + (h * T + tt) * (2 * D) + sub * 4;
-          *reinterpret_cast<uint2*>(plane_row) = phi;
-          *reinterpret_cast<uint2*>(plane_row + D) = plo;
+          if (!copy_evicted) {  // (else the rows are read from the copy)
+            uint16_t* plane_row = hilo + (h * T + tt) * (2 * D) + sub * 4;
+            *reinterpret_cast<uint2*>(plane_row) = phi;
+            *reinterpret_cast<uint2*>(plane_row + D) = plo;
+          }
           for (int k = p; copy && k < fill_end; ++k) {
             uint16_t* dk = gkeys + (base + k) * DCOL + sub * 4;
             *reinterpret_cast<uint2*>(dk) = phi;
@@ -438,7 +441,7 @@ hipError_t run_prepare(const void* keys, int n_heads, int64_t T, int64_t hs, int
                        int64_t PT, int total_blocks, const uint8_t* retained, const int32_t* prank,
                        ProblemMeta* pmeta, const SeqInfo* seqtab, int n_seqs, float* rinv,
                        float* rcol, uint16_t* hilo, uint16_t* pkeys, int32_t* status,
-                       const PrepLevels& lv, hipStream_t st) {
+                       int copy_evicted, const PrepLevels& lv, hipStream_t st) {
   constexpr int ESZ = F32 ? 4 : 2;
   if (total_blocks == 0 || n_heads == 0) return hipSuccess;
   for (int h0 = 0; h0 < n_heads; h0 += 65535) {  // heads along y, in slices the grid holds
@@ -446,7 +449,7 @@ hipError_t run_prepare(const void* keys, int n_heads, int64_t T, int64_t hs, int
     hipLaunchKernelGGL((prepare_keys_kernel<D, F32, LEVELS, ALL>),
                        dim3((unsigned)prep_grid(total_blocks), (unsigned)by), dim3(256), 0, st,
                        (const uint8_t*)keys, T, hs * ESZ, ts * ESZ, PT, retained, prank, pmeta,
-                       seqtab, n_seqs, rinv, rcol, hilo, pkeys, status, h0,
+                       seqtab, n_seqs, rinv, rcol, hilo, pkeys, status, h0, copy_evicted,
                        LEVELS ? nullptr : candidates_of(prank, (int64_t)n_heads * PT),
                        (int64_t)n_heads * PT, total_blocks, lv);
     const hipError_t e = hipGetLastError();
@@ -460,24 +463,24 @@ int prepare_dispatch(const void* keys, int dtype, int d, int n_heads, int64_t T,
                      int64_t head_stride, int64_t token_stride, int64_t PT, int total_blocks,
                      const uint8_t* retained, const int32_t* prank, ProblemMeta* pmeta,
                      const SeqInfo* seqtab, int n_seqs, float* rinv, float* rcol, uint16_t* hilo,
-                     uint16_t* pkeys, int32_t* status, const PrepLevels& lv, void* stream) {
+                     uint16_t* pkeys, int32_t* status, int copy_evicted, const PrepLevels& lv, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   if (dtype == 0 && d == 64)
     return run_prepare<64, false, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                           total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                          rinv, rcol, hilo, pkeys, status, lv, st);
+                                          rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
   if (dtype == 0 && d == 128)
     return run_prepare<128, false, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                            total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                           rinv, rcol, hilo, pkeys, status, lv, st);
+                                           rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
   if (dtype == 1 && d == 64)
     return run_prepare<64, true, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                          total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                         rinv, rcol, hilo, pkeys, status, lv, st);
+                                         rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
   if (dtype == 1 && d == 128)
     return run_prepare<128, true, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                           total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                          rinv, rcol, hilo, pkeys, status, lv, st);
+                                          rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
   return hipErrorInvalidValue;
 }
 
@@ -515,12 +518,13 @@ int launch_prepare_keys(const void* keys, int dtype, int d, int n_heads, int64_t
                         int64_t head_stride, int64_t token_stride, int64_t PT, int total_blocks,
                         const uint8_t* retained, const int32_t* prank, ProblemMeta* pmeta,
                         const SeqInfo* seqtab, int n_seqs, float* rinv, float* rcol,
-                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, int copy_evicted,
-                        void* stream) {
+                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, Sweep sweep, void* stream) {
   const PrepLevels none{nullptr, 0, 1, 0};
-  const auto dispatch = copy_evicted ? prepare_dispatch<false, true> : prepare_dispatch<false, false>;
+  const auto dispatch =
+      sweep == kSweepPairs ? prepare_dispatch<false, true> : prepare_dispatch<false, false>;
   return dispatch(keys, dtype, d, n_heads, T, head_stride, token_stride, PT, total_blocks, retained,
-                  prank, pmeta, seqtab, n_seqs, rinv, rcol, hilo, pkeys, status, none, stream);
+                  prank, pmeta, seqtab, n_seqs, rinv, rcol, hilo, pkeys, status,
+                  sweep == kSweepAll ? 1 : 0, none, stream);
 }
 
 int launch_prepare_keys_levels(const void* keys, int dtype, int d, int n_heads, int64_t T,
@@ -531,7 +535,7 @@ int launch_prepare_keys_levels(const void* keys, int dtype, int d, int n_heads, 
                                void* stream) {
   return prepare_dispatch<true, false>(keys, dtype, d, n_heads, T, head_stride, token_stride, PT,
                                        total_blocks, nullptr, prank, pmeta, seqtab, n_seqs, rinv,
-                                       rcol, hilo, pkeys, status, lv, stream);
+                                       rcol, hilo, pkeys, status, 0, lv, stream);
 }
 
 }  // namespace twinkv

@@ -52,8 +52,8 @@
 //  * Few row blocks leave the chip idle: a row block's columns are then cut into up to 16 segments,
 //    one workgroup each, until 1024 workgroups are in flight (4 per CU: the segments near the end
 //    of the triangle are short).  The candidates merge them like any other workgroups.
-//  * The S0 columns alone (no best_all) are swept by the kernel in sim_retained.hip: the lower half
-//    of a rectangle of S0 x all cannot be shared.
+//  * The S0 columns alone (no best_all) are swept by the kernel in sim_rect.hip: the lower half
+//    of a rectangle of S0 x all cannot be shared.  So are all columns of many short sequences.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -977,7 +977,8 @@ hipError_t run(SimArgs a, hipStream_t st) {
 #define TWINKV_CFG_F32_128 128, true, 1, 2, 4, 2
 #endif
 
-int sim_rows_per_block(int dtype, int d) {
+int sim_rows_per_block(Sweep sweep, int dtype, int d) {
+  if (sweep != kSweepPairs) return sim_rect_rows_per_block(dtype, d);
   if (d != 64 && d != 128) return 0;
   if (dtype == 0) return 4 * 2 * 32;
   if (dtype == 1) return 4 * 1 * 32;
@@ -986,7 +987,7 @@ int sim_rows_per_block(int dtype, int d) {
 
 int launch_sim_reduce(const SimArgs& a, int dtype, int d, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  if (a.counts == nullptr && !a.want_all) return launch_sim_retained(a, dtype, d, st);
+  if (a.sweep != kSweepPairs) return launch_sim_rect(a, dtype, d, st);
   if (dtype == 0 && d == 128) return run<TWINKV_CFG_BF16_128>(a, st);
   if (dtype == 0 && d == 64) return run<TWINKV_CFG_BF16_64>(a, st);
   if (dtype == 1 && d == 64) return run<TWINKV_CFG_F32_64>(a, st);

@@ -48,6 +48,15 @@ inline unsigned long long* candidates_of(const int32_t* prank, int64_t slots) {
       reinterpret_cast<char*>(const_cast<int32_t*>(prank)) + candidates_offset((size_t)slots));
 }
 
+// How the similarity kernel goes over a problem's pairs of tokens.
+enum Sweep {
+  kSweepRetained,  // every row against the S0 columns (sim_rect.hip)
+  kSweepAll,       // every row against all columns (sim_rect.hip)
+  kSweepPairs,     // every unordered pair once, reduced into both tokens (sim_reduce.hip)
+};
+// Which of the last two a call takes that needs all columns (counts: the twin counts), by its shape.
+Sweep sweep_for(int dtype, int d, bool counts, int n_heads, int n_seqs, const int64_t* cu_seqlens);
+
 // Workspace layout shared by the size query and the launchers.
 struct Layout {
   size_t seqtab = 0, rinv = 0, pcol = 0, rcol = 0, prank = 0, pmeta = 0, hilo = 0, pkeys = 0,
@@ -72,14 +81,14 @@ int launch_partition(const uint8_t* retained, const SeqInfo* seqtab, int n_heads
 
 // K1b: one pass over the keys after K1a: r = 1 / ||k|| of every key (fp64 accumulation) to rinv, and
 // the column copy.  A non-finite key sets the problem's flag and status.
-// With copy_evicted (sweeps over all pairs): with g the power of two that brings ||g k|| into
+// kSweepPairs: with g the power of two that brings ||g k|| into
 // (0.5, 1], r / g goes to rcol at the key's column slot, and g k to the slot's place in pkeys (bf16;
 // dcol = 2d bf16 hi/lo for fp32 keys): per problem, 32-slot chunk by chunk, 16-byte piece p of the
 // chunk's column c at byte 512 p + 16 c.  The padding of each list holds copies of its last key, and
 // the candidates at the tokens' slots (candidates_of) are cleared.
-// Without (sweeps over the S0 columns alone): r goes to rcol, and only S0 keys are copied, unscaled,
-// to pkeys[h][PT][dcol] (fp32 keys also go to the row plane hilo [n_heads][T][2d]); the S0 list's
-// last partly filled chunk holds copies of its last key.
+// Else: r goes to rcol, and the keys are copied, unscaled, to pkeys[h][PT][dcol], those of S0 alone for
+// kSweepRetained (whose rows are read from the keys; fp32 keys also go to the row plane hilo
+// [n_heads][T][2d]); a list's last partly filled chunk holds copies of its last key.
 // Tokens one K1b workgroup prepares for this (dtype, d); sequence s owns workgroups
 // [seqtab[s].prep_blk0, seqtab[s].prep_blk0 + ceil(len / that)) of each head.
 int prepare_tokens_per_block(int dtype, int d);
@@ -87,8 +96,7 @@ int launch_prepare_keys(const void* keys, int dtype, int d, int n_heads, int64_t
                         int64_t head_stride, int64_t token_stride, int64_t PT, int total_blocks,
                         const uint8_t* retained, const int32_t* prank, ProblemMeta* pmeta,
                         const SeqInfo* seqtab, int n_seqs, float* rinv, float* rcol,
-                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, int copy_evicted,
-                        void* stream);
+                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, Sweep sweep, void* stream);
 // K1b's grid: x over a head's total_blocks workgroups (padded to prep_grid of them), y over the heads.
 // Workgroups are dispatched round the 8 XCDs in the order x + y * prep_grid.  With many of them each XCD
 // takes a run of the head's tokens, so that the lines two neighbours share meet in one L2; the runs start
@@ -137,7 +145,7 @@ struct SimArgs {
   int n_heads, n_seqs;
   int64_t T, PT;
   int w;
-  int want_all;              // also reduce over evicted columns (best_all / arg_all)
+  Sweep sweep;               // kSweepRetained: best_ret / arg_ret alone
   float tau;                 // count mode: the twin threshold of Eq. 2
   int32_t* counts;           // non-null: count mode, [n_heads][T] twin counts (Eq. 2)
   int max_len;               // longest sequence
@@ -147,19 +155,18 @@ struct SimArgs {
   int32_t* arg_all;
   float* best_ret;
   int32_t* arg_ret;
-  unsigned long long* best;  // [2][n_heads][PT] workspace (unused in count mode): the best candidate
-                             // of each slot over the S0 / evicted columns, value << 32 | ~slot
+  unsigned long long* best;  // kSweepPairs: [2][n_heads][PT] workspace (unused in count mode): the best
+                             // candidate of each slot over the S0 / evicted columns, value << 32 | ~slot
 };
 
-// The sweep over the S0 columns alone (SimArgs::want_all = 0, no counts), and the rows one of its
-// workgroups covers for this (dtype, d).
-int launch_sim_retained(const SimArgs& a, int dtype, int d, void* stream);
-constexpr int sim_retained_rows_per_block(int dtype, int d) {
+// The sweeps of a full rectangle, and the rows one of its workgroups covers for this (dtype, d).
+int launch_sim_rect(const SimArgs& a, int dtype, int d, void* stream);
+constexpr int sim_rect_rows_per_block(int dtype, int d) {
   return dtype == 0 ? (d == 128 ? 384 : d == 64 ? 512 : 0) : (dtype == 1 && (d == 64 || d == 128) ? 128 : 0);
 }
 
-// Rows covered by one workgroup of the all-pairs kernel for this (dtype, d).
-int sim_rows_per_block(int dtype, int d);
+// Rows covered by one workgroup of the sweep for this (dtype, d).
+int sim_rows_per_block(Sweep sweep, int dtype, int d);
 // K2: fused MFMA similarity with the two masked row max / argmax reductions, or (counts set)
 // the per-token twin counts of Eq. 2 over all columns.
 int launch_sim_reduce(const SimArgs& a, int dtype, int d, void* stream);

@@ -70,7 +70,7 @@ int launch_prepare_keys(const void* keys, int dtype, int d, int n_heads, int64_t
                         int64_t head_stride, int64_t token_stride, int64_t PT, int, const uint8_t*,
                         const int32_t* prank, ProblemMeta* pmeta, const SeqInfo* seqtab,
                         int n_seqs, float* rinv, float* rcol, uint16_t* hilo, uint16_t* pkeys,
-                        int32_t*, int, void*) {
+                        int32_t*, Sweep, void*) {
   ++stub::g_launches;
   const int64_t esz = dtype == 1 ? 4 : 2;
   if (T > 0)
@@ -110,7 +110,7 @@ int launch_prepare_keys_levels(const void* keys, int dtype, int d, int n_heads, 
   return 0;
 }
 
-int sim_rows_per_block(int dtype, int d) {
+int sim_rows_per_block(Sweep, int dtype, int d) {
   if (dtype == 0) return d == 128 ? 384 : 512;
   return 128;
 }

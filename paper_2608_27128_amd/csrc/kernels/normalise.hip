@@ -204,9 +204,11 @@ __global__ __launch_bounds__(256) void partition_short_kernel(
 // loads issued before any is used.  blockIdx.y is the head; blockIdx.x runs over the
 // workgroups of all sequences (seqtab[s].prep_blk0 = the first one of sequence s), so no
 // workgroup is launched past the end of a short sequence.  Key reads are nontemporal (each byte is
-// touched once here); the writes are not, as neighbouring workgroups complete each other's lines in
-// L2 (ragged batch of 64 sequences of 1k-4k tokens, 288 heads: 5.3 ms with nontemporal writes, 5.0 ms
-// without; 4.3 ms with the rows written whole, which the sweep then pays for with swizzled, slower
+// touched once here).  So are the writes of whole bf16 rows, issued before the norms are summed (8 heads x
+// 16 sequences of 400-512 tokens, d = 128: 14.9 -> 10.4 us; three levels of 64 heads x 16k: 105 ->
+// 95 us).  The writes for kSweepPairs are not, as neighbouring workgroups complete each other's lines
+// in L2 (ragged batch of 64 sequences of 1k-4k tokens, 288 heads: 5.3 ms with nontemporal writes, 5.0
+// ms without; 4.3 ms with the rows written whole, which the sweep then pays for with swizzled, slower
 // tile loads and uncoalesced row loads).
 constexpr int kPrepIter = 4;
 
@@ -225,6 +227,10 @@ __device__ inline uint4 prep_load16(const uint8_t* p) {
 }
 __device__ inline void prep_store16(char* p, uint4 x) {
   *reinterpret_cast<uint4*>(p) = x;
+}
+__device__ inline void prep_store16_nt(char* p, uint4 x) {
+  const prep_u32x4 v = {x.x, x.y, x.z, x.w};
+  __builtin_nontemporal_store(v, reinterpret_cast<prep_u32x4*>(p));
 }
 
 // LEVELS: the groups of nested retained sets in one pass (PrepLevels): each token goes to
@@ -322,6 +328,10 @@ __global__ __launch_bounds__(256) void prepare_keys_kernel(
     float* const grcol = byte_offset(rcol, goff);
     uint16_t* const gkeys = byte_offset(pkeys, goff);
 
+    if constexpr (!ALL && !F32) {
+      for (int k = p; copy && k < fill_end; ++k)
+        prep_store16_nt(reinterpret_cast<char*>(gkeys + (base + k) * DCOL + sub * 8), raw[it]);
+    }
     double ss = 0.0;
     if constexpr (F32) {
       const float v[4] = {__uint_as_float(raw[it].x), __uint_as_float(raw[it].y),
@@ -378,10 +388,7 @@ __global__ __launch_bounds__(256) void prepare_keys_kernel(
         }
       }
     } else {
-      if constexpr (!ALL) {
-        for (int k = p; copy && k < fill_end; ++k)
-          prep_store16(reinterpret_cast<char*>(gkeys + (base + k) * DCOL + sub * 8), raw[it]);
-      } else {
+      if constexpr (ALL) {
         if (valid) *reinterpret_cast<uint4*>(lds_piece(row, sub)) = scale_bf16x8(raw[it], g);
       }
     }

@@ -54,9 +54,16 @@ int64_t compact_chunks(const int64_t* cu, int n_seqs) {
   return n;
 }
 
+// One level group of twinkv_nn_scores_levels: a sweep over its columns alone.
+constexpr int kOpLevelGroup = -1;
+
 Layout layout_for(int op, int dtype, int d, const Batch& bt, const int64_t* cu = nullptr) {
   Layout L;
   size_t off = 0;
+  // what only some sweeps touch: the pair sweep's candidates (not counting, but a workspace for the
+  // scores is also one for the counts), and the row plane of the sweep over S0 columns alone
+  const bool candidates = op != kOpLevelGroup;
+  const bool row_plane = dtype == TWINKV_F32 && (op == TWINKV_OP_REPAIR || op == kOpLevelGroup);
   if (op == TWINKV_OP_COMPACT) {
     const int64_t nch = compact_chunks(cu, bt.n_seqs);
     L.seqtab = off;
@@ -80,12 +87,15 @@ Layout layout_for(int op, int dtype, int d, const Batch& bt, const int64_t* cu =
     L.rcol = off;
     off = align_up(off + 4 * np);
     L.prank = off;
-    L.best = off + candidates_offset(np);
-    off = align_up(L.best + 16 * np);
+    off = align_up(off + 4 * np);
+    if (candidates) {
+      L.best = off;
+      off = align_up(off + 16 * np);
+    }
     L.pmeta = off;
     off = align_up(off + sizeof(ProblemMeta) * (size_t)bt.n_heads * bt.n_seqs);
     const size_t dcol = dtype == TWINKV_F32 ? (size_t)(2 * d) : (size_t)d;
-    if (dtype == TWINKV_F32) {
+    if (row_plane) {
       L.hilo = off;
       off = align_up(off + 2 * nt * dcol);
     }
@@ -221,7 +231,7 @@ struct Prepared {
 int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const int64_t* cu,
                    const int64_t* budget, int64_t head_stride, int64_t token_stride,
                    const uint8_t* retained, int32_t* status, char* ws, const Layout& L,
-                   Sweep sweep, void* stream, Prepared& P, bool key_prep = true) {
+                   Sweep sweep, int32_t* counts, void* stream, Prepared& P, bool key_prep = true) {
   int total_tiles = 0;
   // the rows of the pair sweep are slots of the column list, counted at its largest padding
   // (both groups end with a partly filled unit); those of the rectangles are tokens
@@ -245,8 +255,11 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   float* rcol = reinterpret_cast<float*>(ws + L.rcol);
   int32_t* prank = reinterpret_cast<int32_t*>(ws + L.prank);
   ProblemMeta* pmeta = reinterpret_cast<ProblemMeta*>(ws + L.pmeta);
-  uint16_t* hilo = dtype == TWINKV_F32 ? reinterpret_cast<uint16_t*>(ws + L.hilo) : nullptr;
+  uint16_t* hilo = dtype == TWINKV_F32 && sweep == kSweepRetained
+                       ? reinterpret_cast<uint16_t*>(ws + L.hilo) : nullptr;
   uint16_t* pkeys = reinterpret_cast<uint16_t*>(ws + L.pkeys);
+  auto* best = sweep == kSweepPairs && counts == nullptr
+                   ? reinterpret_cast<unsigned long long*>(ws + L.best) : nullptr;
 
   int e = launch_partition(retained, dtab, bt.n_heads, bt.n_seqs, bt.T, bt.PT,
                            max_seq_len(cu, bt.n_seqs), pcol, rcol, prank, pmeta, status, stream);
@@ -254,7 +267,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   if (key_prep) {
     e = launch_prepare_keys(keys, dtype, d, bt.n_heads, bt.T, head_stride, token_stride, bt.PT,
                             (int)prep_blocks, retained, prank, pmeta, dtab, bt.n_seqs, rinv, rcol,
-                            hilo, pkeys, status, sweep, stream);
+                            hilo, pkeys, status, sweep, best, counts, stream);
     if (e) return hip_status(e);
   }
 
@@ -290,7 +303,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   a.arg_all = nullptr;
   a.best_ret = nullptr;
   a.arg_ret = nullptr;
-  a.best = reinterpret_cast<unsigned long long*>(ws + L.best);
+  a.best = best;
   return TWINKV_OK;
 }
 
@@ -325,7 +338,7 @@ int run_scores(const void* keys, int dtype, int d, const Batch& bt, const int64_
   const Sweep sweep =
       want_all ? sweep_for(dtype, d, counts != nullptr, bt.n_heads, bt.n_seqs, cu) : kSweepRetained;
   int rc = prepare_scores(keys, dtype, d, bt, cu, budget, head_stride, token_stride, retained,
-                          status, ws, L, sweep, stream, P);
+                          status, ws, L, sweep, counts, stream, P);
   if (rc != TWINKV_OK) return rc;
   *seqtab_dev = P.seqtab;
   if ((rc = record(g_sim_start, stream)) != TWINKV_OK) return rc;
@@ -606,7 +619,7 @@ struct LevelsLayout {
 LevelsLayout levels_layout(int dtype, int d, const Batch& bt, int n_levels, bool want_all) {
   LevelsLayout LL;
   LL.groups = n_levels + (want_all ? 1 : 0);
-  LL.per = align_up(layout_for(TWINKV_OP_NN_SCORES, dtype, d, bt).total);
+  LL.per = align_up(layout_for(kOpLevelGroup, dtype, d, bt).total);
   const size_t n = (size_t)bt.n_heads * (size_t)bt.T;
   size_t off = LL.per * (size_t)LL.groups;
   LL.mask = off;
@@ -646,7 +659,7 @@ int twinkv_nn_scores_levels(const void* keys, int dtype, int d, int n_heads, int
   const LevelsLayout LL = levels_layout(dtype, d, bt, n_levels, want_all);
   if (workspace == nullptr || workspace_bytes < (int64_t)LL.total) return TWINKV_E_WORKSPACE;
   char* base = aligned_base(workspace);
-  const Layout L = layout_for(TWINKV_OP_NN_SCORES, dtype, d, bt);
+  const Layout L = layout_for(kOpLevelGroup, dtype, d, bt);
   const int64_t n = (int64_t)n_heads * bt.T;
   uint8_t* mask = reinterpret_cast<uint8_t*>(base + LL.mask);
   float* gbest = reinterpret_cast<float*>(base + LL.gbest);
@@ -660,7 +673,7 @@ int twinkv_nn_scores_levels(const void* keys, int dtype, int d, int n_heads, int
     if (launch_select_level(level, mask, n, sel, n_levels, stream) != 0) return TWINKV_E_HIP;
     rc = prepare_scores(keys, dtype, d, bt, cu_seqlens, nullptr, head_stride, token_stride, mask,
                         g == 0 ? status : nullptr, base + LL.per * (size_t)g, L,
-                        kSweepRetained, stream, P[g], /*key_prep=*/false);
+                        kSweepRetained, /*counts=*/nullptr, stream, P[g], /*key_prep=*/false);
     if (rc != TWINKV_OK) return rc;
   }
   {

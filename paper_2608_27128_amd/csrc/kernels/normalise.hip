@@ -6,9 +6,9 @@
 //      the bf16 hi/lo split that the similarity sweeps multiply on bf16 MFMA).
 //
 // K1a reads 1 byte and writes 8 bytes per key.  K1b is an HBM stream: it reads d*esize bytes
-// (+5 bytes of mask and rank) and writes d*2 (d*4 for fp32) + 8 bytes per key; for the all-pairs
-// sweep 16 bytes of cleared candidates more, for the S0 sweep only the S0 keys (and fp32 keys' row
-// plane).
+// (+5 bytes of mask and rank) and writes d*2 (d*4 for fp32) + 8 bytes per key; for the pair sweep
+// 16 bytes of cleared candidates more (4 of cleared counts), for the S0 sweep only the S0 keys (and fp32
+// keys' row plane).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -245,7 +245,8 @@ __global__ __launch_bounds__(256) void prepare_keys_kernel(
     ProblemMeta* __restrict__ pmeta, const SeqInfo* __restrict__ seqtab, int n_seqs,
     float* __restrict__ rinv, float* __restrict__ rcol, uint16_t* __restrict__ hilo,
     uint16_t* __restrict__ pkeys, int32_t* __restrict__ status, int h0, int copy_evicted,
-    unsigned long long* __restrict__ best, int64_t plane, int total_blocks, PrepLevels lv) {
+    unsigned long long* __restrict__ best, int32_t* __restrict__ counts, int64_t plane, int total_blocks,
+    PrepLevels lv) {
   constexpr int ESZ = F32 ? 4 : 2;
   constexpr int LPT = D * ESZ / 16;
   constexpr int TPB = 256 / LPT;
@@ -428,9 +429,14 @@ __global__ __launch_bounds__(256) void prepare_keys_kernel(
                      *reinterpret_cast<const uint4*>(lds_piece(row, piece)));
       }
     }
-    // the sweep's candidates of these tokens' slots start empty (padding slots are never read)
+    // the sweep's candidates of these tokens' slots start empty (padding slots are never read), or
+    // the tokens' counts
     if ((int)threadIdx.x < n_all) {
       const int i = threadIdx.x;
+      if (counts != nullptr) {
+        counts[h * T + si.start + t_first + i] = 0;
+        return;
+      }
       const int slot = i < n_here ? rank0 + i : ret_cols + (t_first - rank0) + (i - n_here);
       best[base + slot] = 0ull;
       best[plane + base + slot] = 0ull;
@@ -448,7 +454,8 @@ hipError_t run_prepare(const void* keys, int n_heads, int64_t T, int64_t hs, int
                        int64_t PT, int total_blocks, const uint8_t* retained, const int32_t* prank,
                        ProblemMeta* pmeta, const SeqInfo* seqtab, int n_seqs, float* rinv,
                        float* rcol, uint16_t* hilo, uint16_t* pkeys, int32_t* status,
-                       int copy_evicted, const PrepLevels& lv, hipStream_t st) {
+                       int copy_evicted, unsigned long long* best, int32_t* counts,
+                       const PrepLevels& lv, hipStream_t st) {
   constexpr int ESZ = F32 ? 4 : 2;
   if (total_blocks == 0 || n_heads == 0) return hipSuccess;
   for (int h0 = 0; h0 < n_heads; h0 += 65535) {  // heads along y, in slices the grid holds
@@ -457,8 +464,7 @@ hipError_t run_prepare(const void* keys, int n_heads, int64_t T, int64_t hs, int
                        dim3((unsigned)prep_grid(total_blocks), (unsigned)by), dim3(256), 0, st,
                        (const uint8_t*)keys, T, hs * ESZ, ts * ESZ, PT, retained, prank, pmeta,
                        seqtab, n_seqs, rinv, rcol, hilo, pkeys, status, h0, copy_evicted,
-                       LEVELS ? nullptr : candidates_of(prank, (int64_t)n_heads * PT),
-                       (int64_t)n_heads * PT, total_blocks, lv);
+                       best, counts, (int64_t)n_heads * PT, total_blocks, lv);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -470,24 +476,25 @@ int prepare_dispatch(const void* keys, int dtype, int d, int n_heads, int64_t T,
                      int64_t head_stride, int64_t token_stride, int64_t PT, int total_blocks,
                      const uint8_t* retained, const int32_t* prank, ProblemMeta* pmeta,
                      const SeqInfo* seqtab, int n_seqs, float* rinv, float* rcol, uint16_t* hilo,
-                     uint16_t* pkeys, int32_t* status, int copy_evicted, const PrepLevels& lv, void* stream) {
+                     uint16_t* pkeys, int32_t* status, int copy_evicted, unsigned long long* best,
+                     int32_t* counts, const PrepLevels& lv, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   if (dtype == 0 && d == 64)
     return run_prepare<64, false, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                           total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                          rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
+                                          rinv, rcol, hilo, pkeys, status, copy_evicted, best, counts, lv, st);
   if (dtype == 0 && d == 128)
     return run_prepare<128, false, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                            total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                           rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
+                                           rinv, rcol, hilo, pkeys, status, copy_evicted, best, counts, lv, st);
   if (dtype == 1 && d == 64)
     return run_prepare<64, true, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                          total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                         rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
+                                         rinv, rcol, hilo, pkeys, status, copy_evicted, best, counts, lv, st);
   if (dtype == 1 && d == 128)
     return run_prepare<128, true, LEVELS, ALL>(keys, n_heads, T, head_stride, token_stride, PT,
                                           total_blocks, retained, prank, pmeta, seqtab, n_seqs,
-                                          rinv, rcol, hilo, pkeys, status, copy_evicted, lv, st);
+                                          rinv, rcol, hilo, pkeys, status, copy_evicted, best, counts, lv, st);
   return hipErrorInvalidValue;
 }
 
@@ -525,13 +532,14 @@ int launch_prepare_keys(const void* keys, int dtype, int d, int n_heads, int64_t
                         int64_t head_stride, int64_t token_stride, int64_t PT, int total_blocks,
                         const uint8_t* retained, const int32_t* prank, ProblemMeta* pmeta,
                         const SeqInfo* seqtab, int n_seqs, float* rinv, float* rcol,
-                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, Sweep sweep, void* stream) {
+                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, Sweep sweep,
+                        unsigned long long* best, int32_t* counts, void* stream) {
   const PrepLevels none{nullptr, 0, 1, 0};
   const auto dispatch =
       sweep == kSweepPairs ? prepare_dispatch<false, true> : prepare_dispatch<false, false>;
   return dispatch(keys, dtype, d, n_heads, T, head_stride, token_stride, PT, total_blocks, retained,
                   prank, pmeta, seqtab, n_seqs, rinv, rcol, hilo, pkeys, status,
-                  sweep == kSweepAll ? 1 : 0, none, stream);
+                  sweep == kSweepAll ? 1 : 0, best, counts, none, stream);
 }
 
 int launch_prepare_keys_levels(const void* keys, int dtype, int d, int n_heads, int64_t T,
@@ -542,7 +550,7 @@ int launch_prepare_keys_levels(const void* keys, int dtype, int d, int n_heads, 
                                void* stream) {
   return prepare_dispatch<true, false>(keys, dtype, d, n_heads, T, head_stride, token_stride, PT,
                                        total_blocks, nullptr, prank, pmeta, seqtab, n_seqs, rinv,
-                                       rcol, hilo, pkeys, status, 0, lv, stream);
+                                       rcol, hilo, pkeys, status, 0, nullptr, nullptr, lv, stream);
 }
 
 }  // namespace twinkv

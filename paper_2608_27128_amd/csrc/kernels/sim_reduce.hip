@@ -905,14 +905,6 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
 
 constexpr int kFlatThreads = 256;
 
-// Zero 16-byte pieces (the counts before a sweep; the tail of the last piece is cleared word by
-// word).
-__global__ __launch_bounds__(kFlatThreads) void clear_kernel(uint32_t* __restrict__ p, int64_t words) {
-  const int64_t i = ((int64_t)blockIdx.x * kFlatThreads + threadIdx.x) * 4;
-  for (int e = 0; e < 4; ++e)
-    if (i + e < words) p[i + e] = 0u;
-}
-
 // The candidates of every token to its results: best_ret / arg_ret from plane 0 (S0 columns),
 // best_all / arg_all from both planes.  (Sequences of at most finish_len tokens are done already.)
 __global__ __launch_bounds__(kFlatThreads) void finish_kernel(SimArgs a, int h0) {
@@ -942,9 +934,6 @@ hipError_t run(SimArgs a, hipStream_t st) {
   while (nseg < 16 && rows * nseg < 1024) ++nseg;
   const dim3 block(C::NT), sweep((unsigned)(rows * nseg));
   if (a.counts != nullptr) {
-    const int64_t words = (int64_t)a.n_heads * a.T;
-    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((words + 4 * kFlatThreads - 1) / (4 * kFlatThreads))),
-                       dim3(kFlatThreads), 0, st, reinterpret_cast<uint32_t*>(a.counts), words);
     hipLaunchKernelGGL((sim_reduce_kernel<true, D, SPLIT, NSUB, CPT, BITS, OCC>), sweep, block, 0, st, a, nseg);
     return hipGetLastError();
   }

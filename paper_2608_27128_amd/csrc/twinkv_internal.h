@@ -40,14 +40,6 @@ constexpr int kPermPad = kGroupAlign + kChunk;  // padding per (head, sequence) 
 constexpr int kFlagNonfinite = 1;
 constexpr int kDoneShift = 8;  // flags >> kDoneShift: workgroups of the pair sweep that are done
 
-// The sweep's candidates follow the S0 prefix counts in the workspace: `slots` = n_heads * PT
-// prefix counts, then from the next 256-byte boundary [2][n_heads][PT] 64-bit words (SimArgs::best).
-constexpr size_t candidates_offset(size_t slots) { return (4 * slots + 255) / 256 * 256; }
-inline unsigned long long* candidates_of(const int32_t* prank, int64_t slots) {
-  return reinterpret_cast<unsigned long long*>(
-      reinterpret_cast<char*>(const_cast<int32_t*>(prank)) + candidates_offset((size_t)slots));
-}
-
 // How the similarity kernel goes over a problem's pairs of tokens.
 enum Sweep {
   kSweepRetained,  // every row against the S0 columns (sim_rect.hip)
@@ -85,7 +77,8 @@ int launch_partition(const uint8_t* retained, const SeqInfo* seqtab, int n_heads
 // (0.5, 1], r / g goes to rcol at the key's column slot, and g k to the slot's place in pkeys (bf16;
 // dcol = 2d bf16 hi/lo for fp32 keys): per problem, 32-slot chunk by chunk, 16-byte piece p of the
 // chunk's column c at byte 512 p + 16 c.  The padding of each list holds copies of its last key, and
-// the candidates at the tokens' slots (candidates_of) are cleared.
+// what the sweep merges into is cleared: the candidates at the tokens' slots (best, SimArgs::best), or
+// with counts non-null the tokens' counts [n_heads][T].
 // Else: r goes to rcol, and the keys are copied, unscaled, to pkeys[h][PT][dcol], those of S0 alone for
 // kSweepRetained (whose rows are read from the keys; fp32 keys also go to the row plane hilo
 // [n_heads][T][2d]); a list's last partly filled chunk holds copies of its last key.
@@ -96,7 +89,8 @@ int launch_prepare_keys(const void* keys, int dtype, int d, int n_heads, int64_t
                         int64_t head_stride, int64_t token_stride, int64_t PT, int total_blocks,
                         const uint8_t* retained, const int32_t* prank, ProblemMeta* pmeta,
                         const SeqInfo* seqtab, int n_seqs, float* rinv, float* rcol,
-                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, Sweep sweep, void* stream);
+                        uint16_t* hilo, uint16_t* pkeys, int32_t* status, Sweep sweep,
+                        unsigned long long* best, int32_t* counts, void* stream);
 // K1b's grid: x over a head's total_blocks workgroups (padded to prep_grid of them), y over the heads.
 // Workgroups are dispatched round the 8 XCDs in the order x + y * prep_grid.  With many of them each XCD
 // takes a run of the head's tokens, so that the lines two neighbours share meet in one L2; the runs start
@@ -132,7 +126,7 @@ int launch_prepare_keys_levels(const void* keys, int dtype, int d, int n_heads, 
                                void* stream);
 
 struct SimArgs {
-  const void* keys;          // bf16 keys, or the hi/lo planes for fp32 keys
+  const void* keys;          // (kSweepRetained) bf16 keys, or the hi/lo planes for fp32 keys
   int64_t head_stride;       // elements (of uint16) between heads of `keys`
   int64_t token_stride;      // elements between tokens of `keys`
   const float* rinv;         // [n_heads][T]
@@ -155,8 +149,8 @@ struct SimArgs {
   int32_t* arg_all;
   float* best_ret;
   int32_t* arg_ret;
-  unsigned long long* best;  // kSweepPairs: [2][n_heads][PT] workspace (unused in count mode): the best
-                             // candidate of each slot over the S0 / evicted columns, value << 32 | ~slot
+  unsigned long long* best;  // kSweepPairs without counts: [2][n_heads][PT] workspace, the best candidate
+                             // of each slot over the S0 / evicted columns, value << 32 | ~slot
 };
 
 // The sweeps of a full rectangle, and the rows one of its workgroups covers for this (dtype, d).

@@ -70,8 +70,10 @@ int launch_prepare_keys(const void* keys, int dtype, int d, int n_heads, int64_t
                         int64_t head_stride, int64_t token_stride, int64_t PT, int, const uint8_t*,
                         const int32_t* prank, ProblemMeta* pmeta, const SeqInfo* seqtab,
                         int n_seqs, float* rinv, float* rcol, uint16_t* hilo, uint16_t* pkeys,
-                        int32_t*, Sweep, void*) {
+                        int32_t*, Sweep sweep, unsigned long long* best, int32_t* counts, void*) {
   ++stub::g_launches;
+  touch_out(best, best ? 16 * (int64_t)n_heads * PT : 0);
+  touch_out(counts, counts ? 4 * (int64_t)n_heads * T : 0);
   const int64_t esz = dtype == 1 ? 4 : 2;
   if (T > 0)
     touch(keys, esz * ((int64_t)(n_heads - 1) * head_stride + (T - 1) * token_stride + d));
@@ -81,7 +83,7 @@ int launch_prepare_keys(const void* keys, int dtype, int d, int n_heads, int64_t
   touch(seqtab, (int64_t)sizeof(SeqInfo) * n_seqs);
   touch_out(rinv, 4 * (int64_t)n_heads * T);
   touch_out(rcol, 4 * (int64_t)n_heads * PT);
-  if (dtype == 1) touch_out(hilo, 2 * (int64_t)n_heads * T * dcol);
+  if (dtype == 1 && sweep == kSweepRetained) touch_out(hilo, 2 * (int64_t)n_heads * T * dcol);
   touch_out(pkeys, 2 * (int64_t)n_heads * PT * dcol);
   return 0;
 }
@@ -118,9 +120,10 @@ int sim_rows_per_block(Sweep, int dtype, int d) {
 int launch_sim_reduce(const SimArgs& a, int dtype, int d, void*) {
   ++stub::g_launches;
   const int64_t dcol = dtype == 1 ? 2 * d : d;
-  if (a.T > 0)
+  if (a.T > 0 && a.sweep == kSweepRetained)
     touch(a.keys, 2 * ((int64_t)(a.n_heads - 1) * a.head_stride + (a.T - 1) * a.token_stride + dcol));
   touch(a.rinv, 4 * (int64_t)a.n_heads * a.T);
+  if (a.sweep == kSweepPairs && a.counts == nullptr) touch(a.best, 16 * (int64_t)a.n_heads * a.PT);
   touch(a.pkeys, 2 * (int64_t)a.n_heads * a.PT * dcol);
   touch(a.pcol, 4 * (int64_t)a.n_heads * a.PT);
   touch(a.rcol, 4 * (int64_t)a.n_heads * a.PT);

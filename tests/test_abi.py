@@ -72,6 +72,28 @@ def test_workspace_bytes():
     assert L.twinkv_workspace_bytes(0, 0, 64, 8, 1, None) == -E_NULL
 
 
+def test_workspace_holds_what_the_sweeps_touch():
+    """No candidates (16 bytes a slot) in the level groups, and the fp32 row plane (as large as the keys)
+    only where rows are read from it: the repair over S0 columns alone and the levels."""
+    L = binding.lib()
+    H, n, d = 8, 10000, 64
+    cu = cu_arr([0, n])
+    slots = H * (n + 160)
+    slack = 64 * 1024
+    bf = L.twinkv_workspace_bytes(0, 0, d, H, 1, cu)
+    one = L.twinkv_levels_workspace_bytes(0, d, H, 1, cu, 1, 0)
+    two = L.twinkv_levels_workspace_bytes(0, d, H, 1, cu, 2, 0)
+    group = two - one - 8 * H * n          # a group's slice, without its best values and positions
+    assert abs(bf - 16 * slots - group) < slack
+    extra = 2 * d * slots                  # the lo halves of fp32 columns
+    for op in (0, 3, 4):                   # scores, counts, scorer: no row plane
+        assert abs(L.twinkv_workspace_bytes(op, 1, d, H, 1, cu)
+                   - L.twinkv_workspace_bytes(op, 0, d, H, 1, cu) - extra) < slack, op
+    plane = 4 * d * H * n
+    assert abs(L.twinkv_workspace_bytes(1, 1, d, H, 1, cu)
+               - L.twinkv_workspace_bytes(1, 0, d, H, 1, cu) - extra - plane) < slack
+
+
 def nn(keys=FAKE, dtype=0, d=64, H=2, cu=(0, 100), hs=6400, ts=64, ret=None, w=32,
        ba=FAKE, aa=FAKE, br=None, ar=None, st=None, ws=FAKE, wsb=1 << 40):
     L = binding.lib()

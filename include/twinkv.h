@@ -32,7 +32,7 @@
  * [n_heads][T].  Every entry point enqueues work on `stream` (a hipStream_t passed as void*;
  * NULL = the default stream) and returns without waiting; results are valid once the stream
  * has reached that point.  The small per-sequence table built from the host arrays reaches
- * the workspace as the kernel arguments of upload launches, so the host arrays are consumed
+ * the workspace as the arguments of kernels, so the host arrays are consumed
  * before the call returns and no host memory is read later.  A call enqueues kernel launches
  * only (no memset, no host copy, no allocation), so it may be captured into a HIP graph; a
  * replay repeats the captured batch description (sequence lengths, budgets, tau, w) and

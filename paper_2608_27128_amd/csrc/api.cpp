@@ -247,8 +247,6 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
 
   SeqInfo* dtab = reinterpret_cast<SeqInfo*>(ws + L.seqtab);
   P.seqtab = dtab;
-  if (launch_upload(tab.data(), sizeof(SeqInfo) * tab.size(), dtab, stream) != 0)
-    return TWINKV_E_HIP;
 
   float* rinv = reinterpret_cast<float*>(ws + L.rinv);
   int32_t* pcol = reinterpret_cast<int32_t*>(ws + L.pcol);
@@ -261,7 +259,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   auto* best = sweep == kSweepPairs && counts == nullptr
                    ? reinterpret_cast<unsigned long long*>(ws + L.best) : nullptr;
 
-  int e = launch_partition(retained, dtab, bt.n_heads, bt.n_seqs, bt.T, bt.PT,
+  int e = launch_partition(retained, tab.data(), dtab, bt.n_heads, bt.n_seqs, bt.T, bt.PT,
                            max_seq_len(cu, bt.n_seqs), pcol, rcol, prank, pmeta, status, stream);
   if (e) return hip_status(e);
   if (key_prep) {

@@ -66,8 +66,9 @@ int launch_upload(const void* src, size_t bytes, void* dst, void* stream);
 
 // K1a: stable partition of each problem's positions into [S0 | evicted] column lists from the
 // retained mask: pcol (positions, -1 for padding), prank[t] = number of S0 positions before t
-// (t = 0..len), the per-problem meta, rcol = 0 at padding, status = 0.
-int launch_partition(const uint8_t* retained, const SeqInfo* seqtab, int n_heads, int n_seqs,
+// (t = 0..len), the per-problem meta, rcol = 0 at padding, status = 0.  The sequence table `table` (host)
+// goes to seqtab on the way, for the kernels that follow.
+int launch_partition(const uint8_t* retained, const SeqInfo* table, SeqInfo* seqtab, int n_heads, int n_seqs,
                      int64_t T, int64_t PT, int max_len, int32_t* pcol, float* rcol,
                      int32_t* prank, ProblemMeta* pmeta, int32_t* status, void* stream);
 

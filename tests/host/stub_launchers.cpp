@@ -50,12 +50,12 @@ int launch_upload(const void* src, size_t bytes, void* dst, void*) {
   return 0;
 }
 
-int launch_partition(const uint8_t* retained, const SeqInfo* seqtab, int n_heads, int n_seqs,
-                     int64_t T, int64_t PT, int, int32_t* pcol, float* rcol, int32_t* prank,
+int launch_partition(const uint8_t* retained, const SeqInfo* table, SeqInfo* seqtab, int n_heads,
+                     int n_seqs, int64_t T, int64_t PT, int, int32_t* pcol, float* rcol, int32_t* prank,
                      ProblemMeta* pmeta, int32_t* status, void*) {
   ++stub::g_launches;
   touch(retained, retained ? (int64_t)n_heads * T : 0);  // null: no retained set
-  touch(seqtab, (int64_t)sizeof(SeqInfo) * n_seqs);
+  std::memcpy(seqtab, table, sizeof(SeqInfo) * (size_t)n_seqs);
   touch_out(pcol, 4 * (int64_t)n_heads * PT);
   touch_out(rcol, 4 * (int64_t)n_heads * PT);
   touch_out(prank, 4 * (int64_t)n_heads * PT);

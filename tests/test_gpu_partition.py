@@ -13,3 +13,11 @@ pytestmark = pytest.mark.gpu
 def test_partition_edges(lens, kind):
     batch = synth.make_batch(small_spec(2, list(lens), 64, "bf16", 4, 300 + len(lens) + lens[0] % 7))
     run_and_check(batch, 4, kind, seed=3)
+
+
+@pytest.mark.parametrize("n_seqs", [15, 16, 17])
+def test_table_edges(n_seqs):
+    """Up to 16 sequences the table goes with the partition, beyond that it is uploaded first."""
+    lens = [37 * (s + 1) % 101 for s in range(n_seqs - 1)] + [700]
+    batch = synth.make_batch(small_spec(9, lens, 64, "bf16", 4, 320 + n_seqs))
+    run_and_check(batch, 4, "policy", seed=3)

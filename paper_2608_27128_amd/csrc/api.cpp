@@ -221,7 +221,8 @@ thread_local hipEvent_t g_sim_stop = nullptr;
 
 // K1a + K1b: the sequence table, the column partition and the prepared keys, ready for K2.
 struct Prepared {
-  SimArgs args;         // everything but the outputs, w, want_all and the count mode
+  SimArgs args;         // everything but the outputs, w and the count mode (complete once swept)
+  bool finish_later = false;
   SeqInfo* seqtab = nullptr;
   int prep_blocks = 0;  // K1b workgroups per head
 };
@@ -290,8 +291,7 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
   a.n_seqs = bt.n_seqs;
   a.T = bt.T;
   a.PT = bt.PT;
-  a.max_len = max_seq_len(cu, bt.n_seqs);
-  a.finish_len = 0;
+  a.finish_later = false;
   a.total_tiles = total_tiles;
   a.w = 0;
   a.sweep = sweep;
@@ -318,6 +318,8 @@ int sim_scores(const Batch& bt, int dtype, int d, int w, float* best_all, int32_
   a.arg_all = arg_all;
   a.best_ret = best_ret;
   a.arg_ret = arg_ret;
+  a.finish_later = P.finish_later;
+  P.args = a;
   return hip_status(launch_sim_reduce(a, dtype, d, stream));
 }
 
@@ -325,13 +327,14 @@ int record(hipEvent_t ev, void* stream) {
   return (ev && hipEventRecord(ev, (hipStream_t)stream) != hipSuccess) ? TWINKV_E_HIP : TWINKV_OK;
 }
 
-// K1a + K1b + K2 (shared by nn_scores, repair and the scorer).
+// K1a + K1b + K2 (shared by nn_scores, repair and the scorer).  A caller that passes `finish` goes on with
+// launch_repair: short sequences' results may be left to it (finish->finish_later).
 int run_scores(const void* keys, int dtype, int d, const Batch& bt, const int64_t* cu,
                const int64_t* budget, int64_t head_stride, int64_t token_stride,
                const uint8_t* retained, int w, float* best_all, int32_t* arg_all,
                float* best_ret, int32_t* arg_ret, int32_t* status, char* ws, const Layout& L,
                bool want_all, void* stream, SeqInfo** seqtab_dev, float tau = 0.0f,
-               int32_t* counts = nullptr) {
+               int32_t* counts = nullptr, SimArgs* finish = nullptr) {
   Prepared P;
   const Sweep sweep =
       want_all ? sweep_for(dtype, d, counts != nullptr, bt.n_heads, bt.n_seqs, cu) : kSweepRetained;
@@ -339,9 +342,11 @@ int run_scores(const void* keys, int dtype, int d, const Batch& bt, const int64_
                           status, ws, L, sweep, counts, stream, P);
   if (rc != TWINKV_OK) return rc;
   *seqtab_dev = P.seqtab;
+  P.finish_later = finish != nullptr && sweep == kSweepPairs && max_seq_len(cu, bt.n_seqs) <= kRepairFinishLen;
   if ((rc = record(g_sim_start, stream)) != TWINKV_OK) return rc;
   rc = sim_scores(bt, dtype, d, w, best_all, arg_all, best_ret, arg_ret, tau, counts, P, stream);
   if (rc != TWINKV_OK) return rc;
+  if (finish != nullptr) *finish = P.args;
   return record(g_sim_stop, stream);
 }
 
@@ -445,10 +450,16 @@ int twinkv_repair(const void* keys, int dtype, int d, int n_heads, int n_seqs,
   float* b = best_ret ? best_ret : reinterpret_cast<float*>(ws + L.bbuf);
   const bool want_all = best_all != nullptr || arg_all != nullptr;
   SeqInfo* dtab = nullptr;
+  SimArgs swept;
   rc = run_scores(keys, dtype, d, bt, cu_seqlens, budget, head_stride, token_stride, retained_in,
-                  w, best_all, arg_all, b, arg_ret, nullptr, ws, L, want_all, stream, &dtab);
+                  w, best_all, arg_all, b, arg_ret, nullptr, ws, L, want_all, stream, &dtab, 0.0f, nullptr,
+                  &swept);
   if (rc != TWINKV_OK) return rc;
   RepairArgs ra;
+  if (swept.finish_later) {
+    swept.best_ret = best_ret;  // (b itself stays in the repair kernel)
+    ra.finish = &swept;
+  }
   ra.b = b;
   ra.s0 = retained_in;
   ra.s1 = retained_out;

@@ -1,4 +1,5 @@
-// The exact power-of-two scaling of keys shared by the key preparation and the similarity sweep.
+// The exact power-of-two scaling of keys shared by the key preparation and the similarity sweep, and
+// the similarities that the sweep's packed values stand for.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,6 +27,13 @@ __device__ inline uint4 scale_bf16x8(uint4 raw, float g) {
     o[k] = (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xFFFF0000u);
   }
   return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
+constexpr uint32_t kValidMin = 0x3F800000u;  // packed values >= 1.0f are real candidates
+
+// The similarity that a packed value x stands for, for a token of inverse norm ri.
+__device__ inline float similarity(uint32_t x, float ri) {
+  return (__uint_as_float(x) - 3.0f) * ri / row_scale(ri);
 }
 
 }  // namespace twinkv

@@ -22,6 +22,7 @@
 
 #include "../twinkv_internal.h"
 #include "block_select.h"
+#include "finish.h"
 
 // Threads per problem of the short-sequence path (build-time tuning; 256 measured best
 // against 128 and 512 on 1k-4k-token sequences).
@@ -251,15 +252,24 @@ __device__ inline __amdgpu_buffer_rsrc_t seq_rsrc(const void* base, int nbytes) 
 // measured slower: a problem's rows are rarely 16-byte aligned.)
 constexpr int kShortLen = 4096;
 
-template <int NT>
-__global__ __launch_bounds__(NT, 8) void repair_short_kernel(RepairArgs a) {
-  constexpr int U = kShortLen / NT;
+
+// FINISH: at most kRepairFinishLen tokens, with b from the pair sweep's candidates, which takes the place
+// of the sweep's finish kernel: a launch less, and all candidate loads of a thread in flight together.
+// (GPU time / time of a loop of calls, finish kernel -> here: 1 head x 512 tokens, fp32 26.7 -> 23.8 / 39.5 ->
+// 36.0 us; 8 x 1000, bf16, d = 128 29.5 -> 27.3 us; 288 x 1000 fp32 174 -> 169 us.  With 16 tokens a thread,
+// up to 4096 tokens, it is slower than the kernel: 1 x 4000 34 -> 43 us, 8 x 1000 30 -> 33 us.)
+struct NoFinish {};
+template <int NT, bool FINISH>
+__global__ __launch_bounds__(NT, 8) void repair_short_kernel(
+    RepairArgs a, typename std::conditional<FINISH, SimArgs, NoFinish>::type f) {
+  constexpr int kCap = FINISH ? kRepairFinishLen : kShortLen;
+  constexpr int U = kCap / NT;
   constexpr int NW = NT / 64;
   constexpr int WCAP = 64 * U;  // members one wave can hold
   static_assert(U <= 32, "the S0 and member bits of a thread's slots fit one word each");
   static_assert(NW >= 2, "one wave scans the histogram while another clears the next one");
   // wave w's members of the cut side at s_key[w * WCAP, w * WCAP + its count)
-  __shared__ uint32_t s_key[kShortLen];
+  __shared__ uint32_t s_key[kCap];
   __shared__ int s_hist[2][256];  // digit histograms, used in turn
   __shared__ uint64_t s_red[NW];
   __shared__ uint32_t s_bits[NW][2];  // per wave: AND and OR of its members' keys
@@ -287,7 +297,7 @@ __global__ __launch_bounds__(NT, 8) void repair_short_kernel(RepairArgs a) {
   };
 
 #ifdef TWINKV_DEBUG
-  for (int i = tid; i < kShortLen; i += NT) s_key[i] = ~0u;
+  for (int i = tid; i < kCap; i += NT) s_key[i] = ~0u;
   for (int i = tid; i < 256; i += NT) s_hist[1][i] = -1;
 #endif
   for (int i = tid; i < 256; i += NT) s_hist[0][i] = 0;  // visible after the count barrier
@@ -296,7 +306,19 @@ __global__ __launch_bounds__(NT, 8) void repair_short_kernel(RepairArgs a) {
   // loads return 0 there, so no branches) and count ----
   float x[U];
   uint32_t rb = 0u;  // bit u: token u * NT + tid is in S0
-  {
+  if constexpr (FINISH) {
+    // from the pair sweep's candidates, whose results are written on the way
+    const FinishPlace pl = finish_place(f, h, si, a.pmeta[q]);
+    const __amdgpu_buffer_rsrc_t rs_r = seq_rsrc(s0, len);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      rb |= (uint32_t)(__builtin_amdgcn_raw_buffer_load_b8(rs_r, u * NT + tid, 0, 0) != 0) << u;
+    if (len > 0) {
+      const Scores<U> sc = finish_tokens<U>(f, pl, len, tid, NT);
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = sc.b[u];
+    }
+  } else {
     const __amdgpu_buffer_rsrc_t rs_b = seq_rsrc(b, 4 * len);
     const __amdgpu_buffer_rsrc_t rs_r = seq_rsrc(s0, len);
 #pragma unroll
@@ -798,9 +820,12 @@ int launch_repair(const RepairArgs& a, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const dim3 grid((unsigned)P);
   // the smallest kernel whose slots hold the longest sequence; beyond 32768 tokens, streaming
-  if (a.max_len <= kShortLen)
-    hipLaunchKernelGGL((repair_short_kernel<TWINKV_K3_SHORT_THREADS>), grid,
-                       dim3(TWINKV_K3_SHORT_THREADS), 0, st, a);
+  if (a.finish != nullptr)
+    hipLaunchKernelGGL((repair_short_kernel<TWINKV_K3_SHORT_THREADS, true>), grid,
+                       dim3(TWINKV_K3_SHORT_THREADS), 0, st, a, *a.finish);
+  else if (a.max_len <= kShortLen)
+    hipLaunchKernelGGL((repair_short_kernel<TWINKV_K3_SHORT_THREADS, false>), grid,
+                       dim3(TWINKV_K3_SHORT_THREADS), 0, st, a, NoFinish{});
   else if (a.max_len <= 16384)
     hipLaunchKernelGGL((repair_reg_kernel<1024, 16, TWINKV_K3_16K_LDS_KEYS>), grid, dim3(1024),
                        0, st, a);

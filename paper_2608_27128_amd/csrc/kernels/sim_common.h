@@ -19,8 +19,6 @@ __device__ inline constexpr int slot_row(int v, int half) {
   return 8 * (v >> 2) + 4 * half + (v & 3);
 }
 
-constexpr uint32_t kValidMin = 0x3F800000u;  // packed values >= 1.0f are real candidates
-
 // Fourth dword of a raw buffer resource on gfx9-family parts (32-bit data format).
 constexpr int kBufferFlags = 0x00020000;
 
@@ -94,11 +92,6 @@ __device__ inline bool find_place(const SimArgs& a, int block, Place& pl, int& p
   pl.rowbase = (int64_t)pl.head * a.T + si.start;
   pl.keybase = (int64_t)pl.head * a.head_stride + (int64_t)si.start * a.token_stride;
   return true;
-}
-
-// The similarity that a packed value x stands for, for a token of inverse norm ri.
-__device__ inline float similarity(uint32_t x, float ri) {
-  return (__uint_as_float(x) - 3.0f) * ri / row_scale(ri);
 }
 
 }  // namespace

@@ -58,6 +58,7 @@
 
 #include <type_traits>
 
+#include "finish.h"
 #include "sim_common.h"
 
 namespace twinkv {
@@ -257,41 +258,6 @@ __device__ inline void load_rows(const SimArgs& a, const Place& pl, int row0, in
       rs[v] = !real ? -INFINITY : (r > 0.0f ? -t / r : (a.tau < 0.0f ? INFINITY : -INFINITY));
     }
   }
-}
-
-// In a batch of few problems, sequences of at most kFinishLen tokens get their results from the sweep
-// itself, by the problem's last workgroup, which saves the launch of finish_kernel (one fp32 head of
-// 512 tokens, d = 64: 41.3 -> 38.4 us).  That workgroup works alone, with loads past the caches, so
-// longer sequences are left to the kernel (8 heads of 1000 tokens take 51 us instead of 45, of 2000
-// tokens 81 instead of 47), and so are many problems (2048 of 95-137 tokens: 194 us instead of 186;
-// 288 of 395 tokens: 101 instead of 99).
-constexpr int kFinishLen = 512, kFinishProblems = 64;
-
-// Token i's candidates to its results (rowbase: its sequence's first token in the results; nslots: the
-// slots of its problem's list).  A key with infinite elements makes NaN of a dropped block's zero r', in
-// the row direction also of the zeros past the list's end: a candidate there names no token.
-__device__ inline void finish_token(const SimArgs& a, int64_t colbase, int64_t rowbase, int i, int ret_pad,
-                                    int nslots) {
-  const int r0 = a.prank[colbase + i], r1 = a.prank[colbase + i + 1];
-  const int slot = r1 > r0 ? r0 : ret_pad + (i - r0);
-  const int64_t o = rowbase + i;
-  const float ri = a.rinv[o];
-  u64* best = reinterpret_cast<u64*>(a.best) + colbase;
-  const int32_t* pc = a.pcol + colbase;
-  // (agent scope: in the sweep itself, other workgroups have just merged them)
-  const u64 kr = __hip_atomic_load(best + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const u64 ke = __hip_atomic_load(best + (int64_t)a.n_heads * a.PT + slot, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-  const uint32_t vr = (uint32_t)(kr >> 32), ve = (uint32_t)(ke >> 32);
-  const uint32_t sr = ~(uint32_t)kr, se = ~(uint32_t)ke;
-  const int jr = vr >= kValidMin && sr < (uint32_t)nslots ? pc[sr] : -1;
-  const int je = ve >= kValidMin && se < (uint32_t)nslots ? pc[se] : -1;
-  if (a.best_ret) a.best_ret[o] = jr >= 0 ? similarity(vr, ri) : -1.0f;
-  if (a.arg_ret) a.arg_ret[o] = jr;
-  const bool take_r = jr >= 0 && (je < 0 || vr > ve || (vr == ve && jr < je));
-  const int j = take_r ? jr : je;
-  if (a.best_all) a.best_all[o] = j >= 0 ? similarity(take_r ? vr : ve, ri) : -1.0f;
-  if (a.arg_all) a.arg_all[o] = j;
 }
 
 template <bool COUNT, int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC>
@@ -872,41 +838,12 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
     const int h = r == 0 ? bd.a_hi : (r == 1 ? bd.b_hi : (pad_c > bd.a_hi ? pad_c : -1));
     masked_range(l, h, r == 1 ? grp ^ 1 : grp);
   }
-  if constexpr (COUNT) {
-    counts_out();
-  } else {
-    // The problem's last workgroup to get here turns the candidates of all its tokens into results.
-    // Every workgroup's maxima have reached memory when its waves have waited for them; the counter
-    // is the upper part of the problem's flags (cleared by the partition).
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    // (the arguments are read and the place is found anew: held over the sweep, they would be spilled)
-    auto kernarg = (const __attribute__((address_space(4))) SimArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    int block = (int)blockIdx.x;
-    asm volatile("" : "+s"(block), "+s"(kernarg));
-    const SimArgs b = *(const SimArgs*)kernarg;
-    Place pd;
-    int part;
-    (void)find_place(b, block, pd, part);
-    if (pd.len > b.finish_len) return;
-    __syncthreads();
-    int* const s_done = reinterpret_cast<int*>(smem);
-    if (threadIdx.x == 0) {
-      int32_t* flags = &b.pmeta[pd.problem].flags;
-      *s_done = __hip_atomic_fetch_add(flags, 1 << kDoneShift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >>
-                kDoneShift;
-    }
-    __syncthreads();
-    if (*s_done != (pd.total_chunks * kChunk + C::RB - 1) / C::RB * nseg - 1) return;
-#pragma unroll 2
-    for (int i = threadIdx.x; i < pd.len; i += C::NT)
-      finish_token(b, pd.colbase, pd.rowbase, i, pd.ret_chunks * kChunk, pd.total_chunks * kChunk);
-  }
+  if constexpr (COUNT) counts_out();
 }
 
 constexpr int kFlatThreads = 256;
 
-// The candidates of every token to its results: best_ret / arg_ret from plane 0 (S0 columns),
-// best_all / arg_all from both planes.  (Sequences of at most finish_len tokens are done already.)
+// The candidates of every token to its results.
 __global__ __launch_bounds__(kFlatThreads) void finish_kernel(SimArgs a, int h0) {
   const int64_t t = (int64_t)blockIdx.x * kFlatThreads + threadIdx.x;
   if (t >= a.T) return;
@@ -917,15 +854,12 @@ __global__ __launch_bounds__(kFlatThreads) void finish_kernel(SimArgs a, int h0)
     if (a.seqtab[mid].start <= t) lo = mid; else hi = mid - 1;
   }
   const SeqInfo si = a.seqtab[lo];
-  if (si.len <= a.finish_len) return;
   const ProblemMeta pm = a.pmeta[head * a.n_seqs + lo];
-  finish_token(a, (int64_t)head * a.PT + si.perm_off, (int64_t)head * a.T + si.start, (int)(t - si.start),
-               pm.ret_chunks * kChunk, pm.total_chunks * kChunk);
+  finish_tokens<1>(a, finish_place(a, head, si, pm), si.len, (int)(t - si.start), 0);
 }
 
 template <int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC>
-hipError_t run(SimArgs a, hipStream_t st) {
-  a.finish_len = (int64_t)a.n_heads * a.n_seqs <= kFinishProblems ? kFinishLen : 0;
+hipError_t run(const SimArgs& a, hipStream_t st) {
   using C = Cfg<D, SPLIT, NSUB, CPT, BITS, OCC>;
   const int64_t groups = a.n_heads >= 8 ? 8LL * ((a.n_heads + 7) / 8) : (int64_t)a.n_heads;
   const int64_t rows = groups * a.total_tiles;
@@ -938,8 +872,8 @@ hipError_t run(SimArgs a, hipStream_t st) {
     return hipGetLastError();
   }
   hipLaunchKernelGGL((sim_reduce_kernel<false, D, SPLIT, NSUB, CPT, BITS, OCC>), sweep, block, 0, st, a, nseg);
-  if (a.max_len <= a.finish_len) return hipGetLastError();
   hipError_t e = hipGetLastError();
+  if (a.finish_later) return e;
   for (int h0 = 0; e == hipSuccess && h0 < a.n_heads; h0 += 65535) {
     const int by = a.n_heads - h0 < 65535 ? a.n_heads - h0 : 65535;
     hipLaunchKernelGGL(finish_kernel, dim3((unsigned)((a.T + kFlatThreads - 1) / kFlatThreads), (unsigned)by),

@@ -38,7 +38,6 @@ constexpr int kChunk = 32;           // columns per MFMA chunk (the 32x32x16 til
 constexpr int kGroupAlign = TWINKV_GROUP_ALIGN;
 constexpr int kPermPad = kGroupAlign + kChunk;  // padding per (head, sequence) in the column lists
 constexpr int kFlagNonfinite = 1;
-constexpr int kDoneShift = 8;  // flags >> kDoneShift: workgroups of the pair sweep that are done
 
 // How the similarity kernel goes over a problem's pairs of tokens.
 enum Sweep {
@@ -135,7 +134,7 @@ struct SimArgs {
   const int32_t* pcol;       // [n_heads][PT]
   const float* rcol;         // [n_heads][PT]
   const int32_t* prank;      // [n_heads][PT]: S0 positions before t
-  ProblemMeta* pmeta;        // [n_heads * n_seqs]
+  const ProblemMeta* pmeta;  // [n_heads * n_seqs]
   const SeqInfo* seqtab;     // [n_seqs]
   int n_heads, n_seqs;
   int64_t T, PT;
@@ -143,8 +142,7 @@ struct SimArgs {
   Sweep sweep;               // kSweepRetained: best_ret / arg_ret alone
   float tau;                 // count mode: the twin threshold of Eq. 2
   int32_t* counts;           // non-null: count mode, [n_heads][T] twin counts (Eq. 2)
-  int max_len;               // longest sequence
-  int finish_len;            // (set by the launcher) the sweep writes the results of sequences this short
+  bool finish_later;         // kSweepPairs: the repair turns the candidates into results (RepairArgs::finish)
   int total_tiles;           // row-block tiles of all sequences (sum of nb)
   float* best_all;
   int32_t* arg_all;
@@ -178,8 +176,12 @@ struct RepairArgs {
   int n_sink, n_recent;
   int max_len;               // longest sequence (picks the workgroup size)
   int32_t* stats;            // [n_heads * n_seqs][4]
+  const SimArgs* finish = nullptr;  // (host) nullable
 };
-// K3: orphan / donor classification, radix selection of the m most severe, swap.
+// K3: orphan / donor classification, radix selection of the m most severe, swap.  With finish (sequences of
+// at most kRepairFinishLen tokens), b comes from the candidates of that pair sweep, whose results are
+// written on the way (a.b is not read).
+constexpr int kRepairFinishLen = 1024;
 int launch_repair(const RepairArgs& a, void* stream);
 
 // The body of twinkv_repair_from_scores and of its variant without allocation: validates the

@@ -99,3 +99,28 @@ def test_many_short_problems_counts(d, dtype, lens, tau, w):
     batch = synth.make_batch(small_spec(32, lens, d, dtype, w, 95 + len(lens), dup_frac=0.3))
     counts = host(binding.twin_counts(to_device(batch.keys, dtype), tau, w, batch.cu_seqlens)["counts"])
     check_counts(batch, counts, tau, w)
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "f32")])
+@pytest.mark.parametrize("lens", [(1024, 0, 257, 1), (1023, 255, 256), (1025, 3), (512,), (40,)])
+def test_repair_from_candidates(d, dtype, lens):
+    """Up to 1024 tokens the repair kernel itself turns the pair sweep's candidates into results: the
+    scores' bits, and the repair of those scores, whichever outputs are asked for."""
+    batch = synth.make_batch(small_spec(3, list(lens), d, dtype, 5, 400 + len(lens), dup_frac=0.3))
+    cu = batch.cu_seqlens
+    kt, rt = to_device(batch.keys, dtype), mask_to_device(batch.retained)
+    sc = binding.nn_scores(kt, rt, 5, cu)
+    want = binding.repair_from_scores(sc["best_ret"], rt, batch.budget, 0.9, 2, 3, cu)
+    out = binding.repair(kt, rt, batch.budget, 0.9, 5, 2, 3, cu)
+    some = {k: v.clone().fill_(0) for k, v in out.items() if k in ("s1", "stats", "best_all")}
+    some = binding.repair(kt, rt, batch.budget, 0.9, 5, 2, 3, cu, outputs=some)
+    assert sorted(some) == ["best_all", "s1", "stats"]
+    for k in ("best_ret", "arg_ret", "best_all", "arg_all"):
+        assert np.array_equal(host(out[k]).view(np.int32), host(sc[k]).view(np.int32)), k
+    for k in ("s1", "stats"):
+        assert np.array_equal(host(out[k]), host(want[k])), k
+        assert np.array_equal(host(some[k]), host(want[k])), k
+    assert np.array_equal(host(some["best_all"]), host(sc["best_all"]))
+    inplace = rt.clone()
+    binding.repair(kt, inplace, batch.budget, 0.9, 5, 2, 3, cu, out_mask=inplace)
+    assert np.array_equal(host(inplace), host(want["s1"]))

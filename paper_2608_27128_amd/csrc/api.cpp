@@ -234,10 +234,11 @@ int prepare_scores(const void* keys, int dtype, int d, const Batch& bt, const in
                    const uint8_t* retained, int32_t* status, char* ws, const Layout& L,
                    Sweep sweep, int32_t* counts, void* stream, Prepared& P, bool key_prep = true) {
   int total_tiles = 0;
-  // the rows of the pair sweep are slots of the column list, counted at its largest padding
-  // (both groups end with a partly filled unit); those of the rectangles are tokens
+  // the rows of the pair sweep are slots of the column list, counted at its largest padding (both
+  // groups, or the one group of a call without S0, end with a partly filled unit); those of the
+  // rectangles are tokens
   const int rpb = sim_rows_per_block(sweep, dtype, d);
-  const int row_pad = sweep == kSweepPairs ? kPermPad - 2 : 0;
+  const int row_pad = sweep == kSweepPairs ? (retained ? kPermPad - 2 : kChunk - 1) : 0;
   int64_t prep_blocks = 0;
   std::vector<SeqInfo> tab = seq_table(cu, bt.n_seqs, budget, rpb, total_tiles,
                                        prepare_tokens_per_block(dtype, d), &prep_blocks, row_pad);

@@ -51,7 +51,8 @@ struct Place {
 };
 // Workgroup k (of those of XCD x when there are >= 8 heads: heads h = x (mod 8) go to the XCD the
 // hardware dispatches block b = x (mod 8) to, so one problem's row blocks share that XCD's L2;
-// inside an XCD the sequences run longest first, and a sequence's longest sweeps first).  part
+// inside an XCD the sequences run longest first, and a sequence's longest sweeps first, up to
+// spread_row_block).  part
 // receives the index beyond the row blocks.  False: no such row block.
 __device__ inline bool find_place(const SimArgs& a, int block, Place& pl, int& part) {
   int k, hx, hmax, h0, hstep;
@@ -79,7 +80,7 @@ __device__ inline bool find_place(const SimArgs& a, int block, Place& pl, int& p
   const int nb = a.seqtab[lo].nb;
   const int local = k - hx * a.seqtab[lo].tile_cum;
   pl.head = h0 + hstep * (local / nb);
-  pl.rb = local - (local / nb) * nb;
+  pl.rb = spread_row_block(local - (local / nb) * nb, nb, lo * hx + local / nb, a.n_heads >= 8);
   const int seq = a.seqtab[lo].sorted_seq;
   const SeqInfo si = a.seqtab[seq];
   pl.problem = pl.head * a.n_seqs + seq;

@@ -158,6 +158,20 @@ constexpr int sim_rect_rows_per_block(int dtype, int d) {
   return dtype == 0 ? (d == 128 ? 384 : d == 64 ? 512 : 0) : (dtype == 1 && (d == 64 || d == 128) ? 128 : 0);
 }
 
+// Which of its nb row blocks the problem of ordinal p runs in place i.  A sequence's longest sweeps come
+// first, but workgroups go round the shader engines of an XCD (a problem of >= 8 heads stays on one: own_xcd)
+// or round the XCDs: with an even nb the first row blocks of all problems would meet on some of them and
+// the last ones (often empty, as they are counted for the largest padding) on others.  So the order turns
+// from problem to problem, inside groups of four or two, and across the XCDs as a whole unless it is long.
+// (Repair, d = 128, 4608 problems: 128 tokens, 2 row blocks, 328 -> 236 us; 640 tokens, 4 of them, 1.80 ->
+// 1.16 ms, where 600 tokens with 3 take 1.15; 64 problems of 3700 tokens of 2 heads 323 -> 277 us.)
+constexpr int spread_row_block(int i, int nb, int p, bool own_xcd) {
+  if (nb % 2 != 0) return i;
+  if (own_xcd) return nb % 4 == 0 ? (i & ~3) | ((i + p) & 3) : i ^ ((p >> 1) & 1);
+  if (nb == 2) return i ^ ((p >> 2) & 1);
+  return nb <= 32 ? (i + p) % nb : i;
+}
+
 // Rows covered by one workgroup of the sweep for this (dtype, d).
 int sim_rows_per_block(Sweep sweep, int dtype, int d);
 // K2: fused MFMA similarity with the two masked row max / argmax reductions, or (counts set)

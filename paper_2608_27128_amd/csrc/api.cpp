@@ -166,29 +166,32 @@ std::vector<SeqInfo> seq_table(const int64_t* cu, int n_seqs, const int64_t* bud
 }  // namespace
 
 // The pair sweep does half the products, but pays per problem: its lists are padded to whole groups, a
-// row block of a short list is half idle, its candidates are merged through memory and finished by a
-// kernel of their own, and its copy is written piece by piece.  With many short problems in flight the
-// full rectangle is faster.  The lines lie where the two measured the same over 1200 random batches (1 to
-// 18000 problems, 1 to 12000 tokens, ragged and even); with few problems the pair sweep wins at every
-// length, because it cuts a problem's columns into segments.  Rectangle / pair sweep, us a call:
-// repair of bf16 keys, d = 128, 1024 problems of 160-200 tokens 91 / 132, of 560-700 264 / 386, of
-// 1600-2000 1115 / 1060; 128 problems of 560-700 tokens 66 / 89; d = 64, 4096 of 410-512 448 / 565, 128 of
-// 410-512 63 / 51, 128 of 6400-8000 1040 / 918; counts, d = 128, 1024 of 100-128 57 / 71, of 800-1000
-// 378 / 318; repair of fp32 keys, d = 64, 4096 of 100-128 216 / 266.
+// row block of a short list is half idle, its candidates are merged through memory, and its copy is
+// written piece by piece.  With many short problems in flight the full rectangle is faster; with few, the
+// pair sweep wins at every length, because it cuts a problem's columns into segments.  The lines lie
+// where the two measured the same over 1200 random batches (1 to 18000 problems, 1 to 12000 tokens, ragged
+// and even) and 600 even ones.  Rectangle / pair sweep, us a call: repair of bf16 keys, d = 128, half
+// retained, 288 problems of 96 tokens 39 / 38, of 300 65 / 73, of 900 153 / 153, 4608 of 300 505 / 654;
+// d = 64, 288 of 400 72 / 67, 640 of 400 101 / 108, of 1400, a tenth retained, 345 / 398; counts, d = 128,
+// 288 of 128 28 / 33, of 300 52 / 48, 4608 of 128 204 / 172.
 Sweep sweep_for(int dtype, int d, bool counts, int n_heads, int n_seqs, const int64_t* cu) {
-  struct Short {
-    int problems;     // at least so many of them
-    int mean_tokens;  // of at most so many tokens, in the mean over the tokens (the work goes by it)
+  // the rectangle: for a number of problems, at least so many tokens in all, and sequences of so many
+  // tokens in the mean over the tokens (the work goes by it)
+  struct Range {
+    int64_t problems_min, problems_max, tokens_min, mean_min, mean_max;
   };
-  const Short at = dtype == TWINKV_BF16
-                       ? (d == 128 ? (counts ? Short{96, 256} : Short{96, 1600})
-                                   : (counts ? Short{96, 300} : Short{160, 2500}))
-                       : (d == 128 ? (counts ? Short{96, 100} : Short{48, 100})
-                                   : (counts ? Short{48, 100} : Short{48, 300}));
-  if ((int64_t)n_heads * n_seqs < at.problems) return kSweepPairs;
+  constexpr int64_t kAny = INT64_MAX;
+  const Range at = dtype == TWINKV_BF16
+                       ? (counts ? Range{96, 1024, 0, 0, 140}
+                                 : (d == 128 ? Range{96, kAny, 27000, 140, 800} : Range{384, kAny, 0, 0, 2000}))
+                       : (counts ? Range{kAny, kAny, 0, 0, 0}
+                                 : (d == 128 ? Range{192, kAny, 0, 0, 100} : Range{96, kAny, 0, 0, 128}));
+  const int64_t problems = (int64_t)n_heads * n_seqs, tokens = cu[n_seqs];
+  if (problems < at.problems_min || problems > at.problems_max || n_heads * tokens < at.tokens_min)
+    return kSweepPairs;
   int64_t squares = 0;
   for (int s = 0; s < n_seqs; ++s) squares += (cu[s + 1] - cu[s]) * (cu[s + 1] - cu[s]);
-  return squares <= at.mean_tokens * cu[n_seqs] ? kSweepAll : kSweepPairs;
+  return squares >= at.mean_min * tokens && squares <= at.mean_max * tokens ? kSweepAll : kSweepPairs;
 }
 
 namespace {

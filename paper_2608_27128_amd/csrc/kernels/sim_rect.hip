@@ -744,10 +744,12 @@ hipError_t run(const SimArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)blocks), block(C::NT);
   if (a.sweep == kSweepRetained)
     hipLaunchKernelGGL((sim_rect_kernel<D, SPLIT, NSUB, CPT, OCC, FG, false, false>), grid, block, 0, st, a);
-  else if (a.counts != nullptr)
+  else if (a.counts == nullptr)
+    hipLaunchKernelGGL((sim_rect_kernel<D, SPLIT, NSUB, CPT, OCC, FG, true, false>), grid, block, 0, st, a);
+  else if constexpr (!SPLIT)  // (sweep_for counts fp32 keys over the pairs only)
     hipLaunchKernelGGL((sim_rect_kernel<D, SPLIT, NSUB, CPT, OCC, FG, true, true>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((sim_rect_kernel<D, SPLIT, NSUB, CPT, OCC, FG, true, false>), grid, block, 0, st, a);
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

@@ -68,6 +68,12 @@ typedef unsigned long long u64;
 
 constexpr uint32_t kBias = 0x40400000u;  // 3.0f
 
+// Count mode: a lane keeps a row's count in 8 bits.  The sweep writes them out after kCountChunks chunks,
+// looked at every 32.  The pass after the sweep does after kMaskedCountChunks of a range of chunks, then
+// after kMaskedCountMore further ones; a range can leave all but one of those to the next range's first.
+constexpr int kCountChunks = 192, kMaskedCountChunks = 32, kMaskedCountMore = 224;
+static_assert(kCountChunks + 32 <= 255 && kMaskedCountMore - 1 + kMaskedCountChunks <= 255, "8 bits");
+
 template <int D, bool SPLIT, int NSUB, int CPT, int BITS, int OCC_>
 struct Cfg {
   static constexpr int OCC = OCC_;  // workgroups per CU (waves per SIMD)
@@ -358,7 +364,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
   // candidates, merged with the odd chunk's by one v_max3 (where registers allow).  Count mode:
   // run holds the sign bits of the last 32 chunks (newest in bit 0), kept which of those chunks
   // count, and cnt the counts of the windows before, four rows of 8 bits a register (a lane
-  // counts at most one column per chunk; they are written out every 224 chunks).
+  // counts at most one column per chunk, and they are written out every kCountChunks).
   uint32_t run[NSUB][16], hold[NSUB][16];
   uint32_t cnt[NSUB][4];
   uint32_t kept[NSUB];
@@ -583,7 +589,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
     for (int t = 0; t < C::UF; ++t) fb[t] = read_frag(fbase, t, 0);
 #pragma unroll
     for (int kc = 0; kc < CPT; ++kc) {
-      auto mask_of = [&](int) -> uint32_t { return 0u - ((keep >> kc) & 1u); };
+      const uint32_t mask = 0u - ((keep >> kc) & 1u);
       const float rl = *reinterpret_cast<const float*>(st + C::KEY_BYTES + (kc * kChunk + l32) * 4);
       // (in a vector register: the value mask takes the one scalar operand of v_and_or)
       uint32_t code = LOW - (uint32_t)(c0 + kc - wbase);
@@ -618,8 +624,8 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
           reduce_block(pacc, NSUB - 1, kc == 0 ? true : ((kc - 1) & 1) != 0, prl, pm_mask, pcode, pcb);
           cres = col_result(pcb);
         } else {
-          kept[s - 1] = (kept[s - 1] << 1) | (mask_of(s - 1) & 1u);
-          reduce_block(x, s - 1, (kc & 1) != 0, rl, mask_of(s - 1), code, cb);
+          kept[s - 1] = (kept[s - 1] << 1) | (mask & 1u);
+          reduce_block(x, s - 1, (kc & 1) != 0, rl, mask, code, cb);
         }
 #pragma unroll
         for (int i = 0; i < C::MFMAS; ++i) {
@@ -637,7 +643,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
       pacc = x;
       prl = rl;
       pcode = code;
-      pm_mask = mask_of(NSUB - 1);
+      pm_mask = mask;
       pcb = cb;
     }
   };
@@ -707,12 +713,12 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
     if (close) {
       if constexpr (COUNT) {
         nacc += 32;
-        if (nacc > 190) {  // a lane's counts still fit 8 bits
+        if (nacc >= kCountChunks) {  // a lane's counts still fit 8 bits, with 32 chunks more at the end
           counts_out();
           nacc = 0;
         }
       } else {
-        rows_out(wbase, 1, best0 + (!COUNT && c0 + CPT >= ret_chunks ? plane : 0));
+        rows_out(wbase, 1, best0 + (c0 + CPT >= ret_chunks ? plane : 0));
       }
       open = false;
     }
@@ -741,7 +747,7 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
     if constexpr (COUNT) counts_fold();
   }
   if constexpr (!COUNT) {
-    if (open) rows_out(wbase, 1, best0 + (!COUNT && ta * CPT >= ret_chunks ? plane : 0));
+    if (open) rows_out(wbase, 1, best0 + (ta * CPT >= ret_chunks ? plane : 0));
   }
   finish_tile();
   __syncthreads();
@@ -812,9 +818,9 @@ __global__ __launch_bounds__(kWaves * 64, OCC) void sim_reduce_kernel(SimArgs a,
       if constexpr (COUNT) {
         const uint32_t c = (uint32_t)col_result(cb);
         if (c != 0u) atomicAdd(&counts[col], (int)c);
-        if (++n == 32) {  // a lane's counts still fit 8 bits (at most 224 from the sweep)
+        if (++n == kMaskedCountChunks) {  // a lane's counts still fit 8 bits
           counts_out();
-          n = -192;
+          n -= kMaskedCountMore;
         }
       } else {
         const u64 key = col_key(cb);  // the better of the two halves' rows

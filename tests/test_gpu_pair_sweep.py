@@ -1,7 +1,8 @@
 """The pair sweep (every unordered pair once, reduced into both tokens) at the edges of its tiling:
-row blocks of 128 or 256 slots, 128-slot group alignment, 32-slot chunks, windows of 16 or 64
-chunks in the row direction, column segments (few row blocks) and the XCD-affine order (>= 8
-heads).  Scores and counts against the oracle; the S0-only sweep against the pair sweep."""
+row blocks of 128 or 256 slots, 128-slot group alignment, 32-slot chunks, column segments (few row
+blocks) and the XCD-affine order (>= 8
+heads).  Scores and counts against the oracle; the S0-only sweep against the pair sweep.  Many short problems,
+which take the full rectangle, against the same problems a few at a time."""
 import numpy as np
 import pytest
 
@@ -17,7 +18,7 @@ CASES = [
     # (heads, lens, w, mask)
     (1, EDGES, 0, "policy"),
     (9, EDGES, 40, "policy"),
-    (2, [513, 2049 + 64], 7, "policy"),     # crosses a window of 64 (d = 128) and of 16 chunks
+    (2, [513, 2049 + 64], 7, "policy"),     # (windows of chunks are crossed in test_gpu_long_sweeps.py)
     (1, [2500], 1200, "policy"),            # the window reaches over most row blocks
     (2, [300, 640], 3, "one"),
     (2, [300, 640], 3, "all"),

@@ -29,6 +29,7 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 SIM_SOURCE = os.path.join(ROOT, "paper_2608_27128_amd", "csrc", "kernels", "sim_reduce.hip")
+RECT_SOURCE = os.path.join(ROOT, "paper_2608_27128_amd", "csrc", "kernels", "sim_rect.hip")
 COMPACT_SOURCE = os.path.join(ROOT, "paper_2608_27128_amd", "csrc", "kernels", "compact.hip")
 
 
@@ -524,7 +525,12 @@ def main() -> int:
         pairs = float(sp.n_heads * np.sum(lens * np.asarray(batch.budget, dtype=np.float64)))
     else:
         pairs = float(sp.n_heads * np.sum(lens * lens))  # ordered key pairs per step
-    flops = 2.0 * batch.d * pairs                         # dense masked K K^T (the kernel multiplies each unordered pair once)
+    # flops the similarity kernel executes: the S0 sweep multiplies rows x S0 columns, the pair sweep each
+    # row block of 256 (fp32 keys: 128) slots with the columns from its own on
+    pair_sweep = args.path != "repair_s0"
+    block = 256 if batch.dtype == "bf16" else 128
+    executed = float(sp.n_heads * np.sum(0.5 * lens * (lens + block))) if pair_sweep else pairs
+    flops = 2.0 * batch.d * executed
 
     if args.path == "compact":
         return compact_bench(args, sp, batch, keys, ret, dev)
@@ -609,11 +615,15 @@ def main() -> int:
         "repair_ms_per_cache": ms_per_step,
         "step_ms_events": {"median": float(np.median(step_ms)), "min": float(np.min(step_ms)),
                            "max": float(np.max(step_ms))},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
+        "roofline": {"bound": "valu" if pair_sweep else "mfma", "achieved": achieved,
+                     "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                      "traffic": profiled_traffic(sp.name, "repair_pass" if args.path == "repair"
-                                                 else f"{args.path}_pass"),
-                     "kernel": "sim_rect_kernel" if args.path == "repair_s0" else "sim_reduce_kernel",
+                                                 else f"{args.path}_pass",
+                                                 source=SIM_SOURCE if pair_sweep else RECT_SOURCE),
+                     "kernel": "sim_reduce_kernel" if pair_sweep else "sim_rect_kernel",
+                     # 2 d flops per ordered pair, of which the pair sweep executes about half
+                     "ordered_pair_tflops": 2.0 * batch.d * pairs / (k2_ms * 1e-3) / 1e12,
                      "kernel_ms": k2_ms,
                      "kernel_ms_median": float(np.median(k2_each)),
                      "kernel_ms_min": float(np.min(k2_each)),

@@ -33,13 +33,14 @@
 //    The 64-bit candidates order by value, then by the smaller slot (the smaller position inside
 //    its group), so results do not depend on the order of the merges.
 //  * Cost per pair of tokens: 5 VALU instructions per lane element (two v_fma, two v_and_or, two
-//    halves of a v_max3) beside half the MFMA work of a full square.  The sweep is bound by the VALU
-//    (75% busy at d = 128, 32k tokens); with every ordered pair on its own it was bound by the MFMA
-//    (1313 of the 1340 TFLOP/s a large matrix product reaches).
-//  * Measured, full square -> upper triangle, this kernel alone: 288 heads x 32k, d = 128
-//    60.3 -> 41.7 ms; 288 heads x 64 ragged sequences of 1k-4k 29.3 -> 24.7 ms; 8 heads x 4001
-//    101 -> 40 us; 128 heads x 8k, d = 64 1193 -> 1162 us (half the MFMA work per pair, the same
-//    VALU work); counting, 288 x 16k 14.7 -> 9.1 ms.  Two waves per SIMD: with one, nothing hides
+//    halves of a v_max3) beside half the MFMA work of a full square.  The sweep is bound by VALU
+//    issue (VALU busy 69% of the cycles and MFMA 46% at d = 128, 32k tokens; 78% and 23% at d = 64, 8k;
+//    63% and 35% on 1k-4k ragged sequences); with every ordered pair on its own it was bound by the
+//    MFMA (1313 of the 1340 TFLOP/s a large matrix product reaches).
+//  * Measured, full square -> upper triangle, whole calls: 288 heads x 32k, d = 128 59.6 -> 43.1 ms
+//    (this kernel 41.8); 288 heads x 64 ragged sequences of 1k-4k 33.7 -> 30.3 ms (this kernel 23.7, the
+//    key preparation 4.8, finishing 0.7); 8 heads x 4001 123 -> 62 us; 128 heads x 8k, d = 64 1152 -> 1103 us (half the MFMA work per pair,
+//    the same VALU work); counting and eviction, 288 x 16k 14.8 -> 9.3 ms.  Two waves per SIMD: with one, nothing hides
 //    the row direction's serial maxima (NSUB 2 and 4, both slower); with three the 2 x 16 running
 //    maxima per row block do not fit.
 //  * Products of bf16 values are exact in fp32; accumulation is fp32.  fp32 keys use the
@@ -54,6 +55,7 @@
 //    of the triangle are short).  The candidates merge them like any other workgroups.
 //  * The S0 columns alone (no best_all) are swept by the kernel in sim_rect.hip: the lower half
 //    of a rectangle of S0 x all cannot be shared.  So are all columns of many short sequences.
+//  * The candidates become results in finish_kernel, or in the repair kernel of short sequences.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

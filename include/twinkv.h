@@ -332,7 +332,7 @@ int twinkv_compact(const void* keys, const void* values, int dtype, int d, int n
  * Profiling hook.  For calls made afterwards from the calling thread, record the given
  * hipEvent_t handles on the call's stream immediately before and immediately after the
  * launch of the call's main kernel -- the similarity kernel (the fused contraction +
- * reductions), or in twinkv_compact the row gather -- so its duration can be read with
+ * reductions, with the short kernel that may follow it to write the results), or in twinkv_compact the row gather -- so its duration can be read with
  * hipEventElapsedTime.  The events stay owned by the caller; pass NULL, NULL to
  * stop recording.
  */

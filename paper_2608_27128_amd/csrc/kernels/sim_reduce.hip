@@ -38,8 +38,8 @@
 //    63% and 35% on 1k-4k ragged sequences); with every ordered pair on its own it was bound by the
 //    MFMA (1313 of the 1340 TFLOP/s a large matrix product reaches).
 //  * Measured, full square -> upper triangle, whole calls: 288 heads x 32k, d = 128 59.6 -> 43.1 ms
-//    (this kernel 41.8); 288 heads x 64 ragged sequences of 1k-4k 33.7 -> 30.3 ms (this kernel 23.7, the
-//    key preparation 4.8, finishing 0.7); 8 heads x 4001 123 -> 62 us; 128 heads x 8k, d = 64 1152 -> 1103 us (half the MFMA work per pair,
+//    (this kernel 41.8); 288 heads x 64 ragged sequences of 1k-4k 34.4 -> 29.4 ms (this kernel 23.7, the
+//    key preparation 4.8, finishing 0.7); 8 heads x 4001 123 -> 62 us; 128 heads x 8k, d = 64 1186 -> 1100 us (half the MFMA work per pair,
 //    the same VALU work); counting and eviction, 288 x 16k 14.8 -> 9.3 ms.  Two waves per SIMD: with one, nothing hides
 //    the row direction's serial maxima (NSUB 2 and 4, both slower); with three the 2 x 16 running
 //    maxima per row block do not fit.
